@@ -28,13 +28,14 @@ PREC_MIXED_BF16 = 1
 PREC_MIXED_FP16 = 2
 PREC_MIXED_FP32 = 3
 # Launch configurations behind the tile indices of kbl_autotune_bounds
-# (FP64 2D: threads BX x BY, nodes per thread TX x TY, table mode; mixed 2D:
+# (FP64 2D: threads BX x BY, nodes per thread TX x TY, table mode, where mode
+# 3 is the culling kernel with one element per wave; mixed 2D:
 # x tiles per wave, y k-steps, waves per workgroup).
 FP64_TILES = {0: (16, 16, 1, 1, 0), 1: (16, 16, 2, 2, 0), 2: (16, 16, 3, 3, 0),
               3: (16, 16, 3, 3, 1), 4: (16, 8, 3, 6, 0), 5: (16, 16, 4, 4, 0),
               6: (16, 16, 4, 4, 1), 7: (32, 8, 2, 8, 1), 8: (16, 16, 2, 4, 0),
               9: (16, 16, 4, 2, 0), 10: (16, 16, 2, 2, 2), 11: (16, 16, 3, 3, 2),
-              12: (16, 16, 4, 4, 2), 13: (16, 8, 3, 6, 2)}
+              12: (16, 16, 4, 4, 2), 13: (16, 8, 3, 6, 2), 14: (16, 16, 4, 4, 3)}
 # d = 3 tiles: (BX, BY, BZ, TX, TY, TZ) covers nx <= BX TX, ny <= BY TY, any nz
 FP64_TILES_3D = {0: (8, 8, 4, 2, 2, 2), 1: (8, 8, 4, 3, 3, 1), 2: (16, 16, 1, 2, 2, 2),
                  3: (16, 16, 1, 3, 3, 1), 4: (16, 16, 1, 4, 4, 1), 5: (8, 8, 4, 2, 2, 4),

@@ -813,6 +813,12 @@ hipError_t launch_2d(const BoundsArgs& a, hipStream_t stream) {
     return launch(bounds_fp64_2d<BX, BY, TX, TY, BTAB>, BX * BY, a, stream);
 }
 
+// mode 3: the kernel that culls states block by block
+template <>
+hipError_t launch_2d<16, 16, 4, 4, 3>(const BoundsArgs& a, hipStream_t stream) {
+    return launch_bounds_cull_2d(a, stream);
+}
+
 #define KBL_TILE(BX, BY, TX, TY, M) {BX, BY, TX, TY, M, launch_2d<BX, BY, TX, TY, M>}
 constexpr Tile2D kTiles2D[] = {
     KBL_TILE(16, 16, 1, 1, 0),   // 0: n <= 16
@@ -829,8 +835,10 @@ constexpr Tile2D kTiles2D[] = {
     KBL_TILE(16, 16, 3, 3, 2),   // 11: n <= 48, A and B from LDS
     KBL_TILE(16, 16, 4, 4, 2),   // 12: n <= 64, A and B from LDS
     KBL_TILE(16, 8, 3, 6, 2),    // 13: n <= 48, two waves, A and B from LDS
+    KBL_TILE(16, 16, 4, 4, 3),   // 14: n <= 64, states culled block by block
 };
 #undef KBL_TILE
+constexpr int kCullTile = 14;
 constexpr int kNumTiles2D = sizeof(kTiles2D) / sizeof(kTiles2D[0]);
 
 // Defaults from a measured sweep: with A, A + l and B read from LDS tables
@@ -842,6 +850,21 @@ int default_tile_2d(int nx, int ny) {
     if (n <= 32) return 1;
     if (n <= 48) return 11;
     return 12;
+}
+
+// Whether the culling kernel (tile 14) is the default.  It walks one element
+// per wave, so it needs a few thousand elements to fill the chip, and its
+// gain grows with the grid (blocks become small against the width of the
+// Maxwellians) and with the stencil.
+bool cull_pays(const BoundsArgs& a) {
+    if (!bounds_cull_fits(a)) return false;
+    const int n = a.nx > a.ny ? a.nx : a.ny;
+    if (n <= 24 || a.n_elem < 6000) return false;
+    if (n > 48) return true;
+    const int hw = (a.nx + 15) / 16, hh = (a.ny + 15) / 16;
+    const int blocks = ((a.nx + 2 * hw - 1) / (2 * hw)) * ((a.ny + 2 * hh - 1) / (2 * hh));
+    if (blocks <= 8 * (64 / (hw * hh))) return true;
+    return a.n_elem >= 16384 && a.nnz * a.n_s >= 64 * a.n_elem;
 }
 
 }  // namespace
@@ -877,7 +900,15 @@ hipError_t launch_bounds_fp64_energy(const BoundsArgs& a, int dim, hipStream_t s
 hipError_t launch_bounds_fp64(const BoundsArgs& a, int dim, hipStream_t stream, int tile) {
     if (a.n_elem == 0) return hipSuccess;
     if (dim == 2) {
-        if (tile < 0) tile = default_tile_2d(a.nx, a.ny);
+        if (tile < 0) {
+            if (cull_pays(a)) {
+                // one element per wave on small meshes (less of a tail)
+                BoundsArgs b = a;
+                if (a.grid_blocks == -2 && a.n_elem < 65536) b.grid_blocks = -1;
+                return launch_bounds_cull_2d(b, stream);
+            }
+            tile = default_tile_2d(a.nx, a.ny);
+        }
         if (!bounds_tile_fits_2d(tile, a.nx, a.ny)) return hipErrorInvalidValue;
         return kTiles2D[tile].fn(a, stream);
     }

@@ -99,6 +99,9 @@ hipError_t launch_bounds_fp64_3d(const BoundsArgs& a, hipStream_t stream, int ti
 int bounds_tile_count_3d();
 bool bounds_tile_fits_3d(int tile, int nx, int ny, int nz);
 int bounds_default_tile_3d(int nx, int ny, int nz);
+// The 2D kernel that culls states block by block (one wave per element).
+hipError_t launch_bounds_cull_2d(const BoundsArgs& a, hipStream_t stream);
+bool bounds_cull_fits(const BoundsArgs& a);
 int bounds_tile_count_2d();
 bool bounds_tile_fits_2d(int tile, int nx, int ny);
 int mixed_tile_count();
