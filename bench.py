@@ -71,6 +71,7 @@ KERNEL_SOURCES = {
         "paper_2407_20966_amd/csrc/bounds_common.h",
         "paper_2407_20966_amd/csrc/kbl_internal.h", "paper_2407_20966_amd/csrc/exp2_table.h"),
     3: ("paper_2407_20966_amd/csrc/bounds_fp64_3d.hip",
+        "paper_2407_20966_amd/csrc/bounds_cull_3d.hip",
         "paper_2407_20966_amd/csrc/bounds_common.h", "paper_2407_20966_amd/csrc/kbl_internal.h",
         "paper_2407_20966_amd/csrc/exp2_table.h"),
 }
@@ -224,33 +225,40 @@ def pair_ops(dim: int) -> int:
     return 8 if dim == 1 else 6
 
 
-# The 2D kernel that culls stencil states block by block evaluates a
-# data-dependent share of the pairs.  Its roofline counts only what it does
-# for any data, in VALU lane-ops: 10 + 27 per (state, block of the velocity
-# grid) to find the block's reference states and to bound a state against
-# them, and 4 exps of 13 ops and 6 fma per velocity node.
-CULL_OPS_PER_STATE_BLOCK = 37
-CULL_OPS_PER_NODE = 58
+# The 2D and 3D kernels that cull stencil states block by block evaluate a
+# data-dependent share of the pairs.  Their roofline counts only what they do
+# for any data, in VALU lane-ops: per (state, block of the velocity grid) 10
+# (2D; 11 in 3D) to find the block's reference states and 27 (33) to bound a
+# state against them, and per velocity node 4 exps of 13 ops and 6 (8) fma.
+CULL_OPS_PER_STATE_BLOCK = {2: 37, 3: 44}
+CULL_OPS_PER_NODE = {2: 58, 3: 60}
+CULL_TILE = {2: 14, 3: 9}
 
 
 def cull_ops(wl) -> float:
-    """Data-independent VALU lane-ops of one culled 2D bounds pass."""
+    """Data-independent VALU lane-ops of one culled bounds pass."""
     blocks = 1
-    for n in wl.grid.n[:2]:
-        b = 2 * -(-n // 16)
+    for n in wl.grid.n[: wl.dim]:
+        b = 2 * -(-n // 16) if wl.dim == 2 else (4 if n <= 32 else 8)
         blocks *= -(-n // b)
     states = float(wl.stencil_sizes().sum()) * wl.n_s
-    return states * blocks * CULL_OPS_PER_STATE_BLOCK + float(wl.n_elem) * wl.n_vel() * CULL_OPS_PER_NODE
+    return (states * blocks * CULL_OPS_PER_STATE_BLOCK[wl.dim]
+            + float(wl.n_elem) * wl.n_vel() * CULL_OPS_PER_NODE[wl.dim])
 
 
 def is_culled(wl, tuned) -> bool:
     """Whether the FP64 bounds launch is the culling kernel (an autotuned
-    choice, or the default on large meshes)."""
-    if wl.dim != 2:
+    choice, or the default on large meshes and grids)."""
+    if wl.dim == 1:
         return False
     if tuned:
-        return tuned["tile"] == 14
-    return max(wl.grid.n[:2]) > 24 and wl.n_elem >= 16384
+        return tuned["tile"] == CULL_TILE[wl.dim]
+    return max(wl.grid.n[:2]) > (24 if wl.dim == 2 else 16) and wl.n_elem >= 16384
+
+
+def cull_note(dim: int) -> str:
+    return (f"{CULL_OPS_PER_STATE_BLOCK[dim]} per (state, block) and {CULL_OPS_PER_NODE[dim]} per "
+            "velocity node; the pairs evaluated after the cull are not counted")
 
 
 # Mixed precision (FP32 envelopes, 2D): the same two adds per pair, but the
@@ -286,6 +294,8 @@ def kernel_shape(kbl, dim, tuned, n_elem, n_cu):
                 blocks = kbl._lib.launch_workgroups({"elements_per_workgroup": k}, n_elem, n_cu)
             return "bounds_cull_2d", blocks * bx * by
         return f"bounds_fp64_2d<{bx}, {by}, {tx}, {ty}, {md}>", blocks * bx * by
+    if tuned["tile"] == CULL_TILE[3]:
+        return "bounds_cull_3d", blocks * 256
     bx, by, bz, tx, ty, tz = kbl._lib.FP64_TILES_3D[tuned["tile"]]
     return f"bounds_fp64_3d<{bx}, {by}, {bz}, {tx}, {ty}, {tz}>", blocks * bx * by * bz
 
@@ -511,7 +521,8 @@ def time_3d(args, kbl, torch, synth, stream):
     l_ms = float(np.mean([e[1].elapsed_time(e[2]) for e in ev]))
     n_cu = torch.cuda.get_device_properties(dev).multi_processor_count
     kname, gthreads = kernel_shape(kbl, 3, tuned, wl.n_elem, n_cu)
-    ops = wl.pairs() * pair_ops(3)
+    culled = is_culled(wl, tuned)
+    ops = cull_ops(wl) if culled else wl.pairs() * pair_ops(3)
     print(f"[bench] hex32: {ms:.3f} ms/step (bounds {b_ms:.3f} ms, limit {l_ms:.3f} ms)",
           file=sys.stderr, flush=True)
     traffic, traffic_grid = (profiled_traffic(kname, gthreads, "hex32", 3) if gthreads
@@ -523,6 +534,8 @@ def time_3d(args, kbl, torch, synth, stream):
            "frac": ops / (b_ms * 1e-3) / VALU_PEAK_OPS, "traffic": traffic,
            "traffic_unit": "bytes per launch", "traffic_grid_threads": traffic_grid, "launch": tuned,
            "parity_tol": 1e-12}
+    if culled:
+        out["ops_counted"] = cull_note(3)
     del st, tg, lim
     return out
 
@@ -664,9 +677,7 @@ def fp64_leg(args, kbl, torch, d, stream, n_cu, label, steps):
             "ops_per_pair": pair_ops(wl.dim), "kernel_ms": b_ms, "limit_ms": l_ms,
             "limit_hbm_frac": limit_hbm_frac(d, l_ms)}
     if culled:
-        roof["ops_counted"] = (f"{CULL_OPS_PER_STATE_BLOCK} per (state, block) and "
-                               f"{CULL_OPS_PER_NODE} per velocity node; the pairs evaluated "
-                               "after the cull are not counted")
+        roof["ops_counted"] = cull_note(wl.dim)
         roof["pair_rate_vs_evaluating_all"] = (wl.pairs() * pair_ops(wl.dim) / (b_ms * 1e-3)
                                                / VALU_PEAK_OPS)
     return {"ms_per_step": ms, "value": wl.n_elem / (ms * 1e-3), "unit": "elements/s",

@@ -37,9 +37,10 @@ FP64_TILES = {0: (16, 16, 1, 1, 0), 1: (16, 16, 2, 2, 0), 2: (16, 16, 3, 3, 0),
               9: (16, 16, 4, 2, 0), 10: (16, 16, 2, 2, 2), 11: (16, 16, 3, 3, 2),
               12: (16, 16, 4, 4, 2), 13: (16, 8, 3, 6, 2), 14: (16, 16, 4, 4, 3)}
 # d = 3 tiles: (BX, BY, BZ, TX, TY, TZ) covers nx <= BX TX, ny <= BY TY, any nz
+# (9 is the culling kernel)
 FP64_TILES_3D = {0: (8, 8, 4, 2, 2, 2), 1: (8, 8, 4, 3, 3, 1), 2: (16, 16, 1, 2, 2, 2),
                  3: (16, 16, 1, 3, 3, 1), 4: (16, 16, 1, 4, 4, 1), 5: (8, 8, 4, 2, 2, 4),
-                 6: (8, 8, 4, 3, 3, 2), 7: (8, 8, 4, 4, 4, 1), 8: (16, 16, 1, 3, 3, 2)}
+                 6: (8, 8, 4, 3, 3, 2), 7: (8, 8, 4, 4, 4, 1), 8: (16, 16, 1, 3, 3, 2), 9: (8, 8, 4, 8, 8, 2)}
 MIXED_TILES = {0: (1, 1, 1), 1: (2, 2, 1), 2: (1, 2, 2), 3: (3, 3, 1), 4: (1, 3, 3),
                5: (2, 4, 2), 6: (1, 4, 4)}
 # launch shapes of kbl_autotune_bounds' result (8 * tile + shape)

@@ -374,14 +374,15 @@ __attribute__((amdgpu_waves_per_eu(3))) void bounds_cull_2d(BoundsArgs p, CullGr
                                 qi[i][j] = v[i][j] + ra.l;
                             }
                     }
-                    for (int k = 1; __any(k < n); k += 2) {
-                        ra = L.rec[nx];
-                        nx = next();
-                        take(rb);
-                        if (!__any(k + 1 < n)) break;
-                        rb = L.rec[nx];
-                        nx = next();
-                        take(ra);
+                    int k = 1;
+                    if (__builtin_amdgcn_ballot_w64(k < n)) {
+                        do {
+                            ra = rb;
+                            rb = L.rec[nx];
+                            nx = next();
+                            take(ra);
+                            ++k;
+                        } while (__builtin_amdgcn_ballot_w64(k < n));
                     }
                 };
                 side(std::true_type{}, qx, qix);

@@ -325,6 +325,12 @@ hipError_t launch_3d(const BoundsArgs& a, hipStream_t stream) {
     return hipGetLastError();
 }
 
+// the kernel that culls states block by block (2 x 2 x 2 nodes per thread)
+template <>
+hipError_t launch_3d<8, 8, 4, 8, 8, 2>(const BoundsArgs& a, hipStream_t stream) {
+    return launch_bounds_cull_3d(a, stream);
+}
+
 #define KBL_TILE3(BX, BY, BZ, TX, TY, TZ) \
     {BX, BY, BZ, TX, TY, TZ, launch_3d<BX, BY, BZ, TX, TY, TZ>}
 constexpr Tile3D kTiles3D[] = {
@@ -337,9 +343,21 @@ constexpr Tile3D kTiles3D[] = {
     KBL_TILE3(8, 8, 4, 3, 3, 2),     // 6: nx, ny <= 24, slabs of 8
     KBL_TILE3(8, 8, 4, 4, 4, 1),     // 7: nx, ny <= 32, slabs of 4
     KBL_TILE3(16, 16, 1, 3, 3, 2),   // 8: nx, ny <= 48, slabs of 2
+    KBL_TILE3(8, 8, 4, 8, 8, 2),     // 9: n <= 64, states culled block by block
 };
 #undef KBL_TILE3
+constexpr int kCullTile3 = 9;
 constexpr int kNumTiles3D = sizeof(kTiles3D) / sizeof(kTiles3D[0]);
+
+// Whether the culling kernel (tile 9) is the default.  Grids of up to 16 nodes
+// in x and y have blocks of a quarter of the box (lists of most states: 0.8 of
+// tile 0's speed at 16^3 and 189 states); a few hundred elements do not fill
+// the chip, and its latency per element is the longer one unless the grid is
+// large (125 elements: 0.9 of the default tile at 24^3 nodes, 2.5 times at 64^3).
+bool cull_pays_3d(const BoundsArgs& a) {
+    const int n = a.nx > a.ny ? a.nx : a.ny;
+    return bounds_cull_fits_3d(a) && (n > 32 || (n > 16 && a.n_elem >= 512));
+}
 
 }  // namespace
 
@@ -366,7 +384,8 @@ int bounds_default_tile_3d(int nx, int ny, int nz) {
 
 hipError_t launch_bounds_fp64_3d(const BoundsArgs& a, hipStream_t stream, int tile) {
     if (a.n_elem == 0) return hipSuccess;
-    if (tile < 0) tile = bounds_default_tile_3d(a.nx, a.ny, a.nz);
+    if (tile < 0)
+        tile = cull_pays_3d(a) ? kCullTile3 : bounds_default_tile_3d(a.nx, a.ny, a.nz);
     if (!bounds_tile_fits_3d(tile, a.nx, a.ny, a.nz)) return hipErrorInvalidValue;
     return kTiles3D[tile].fn(a, stream);
 }

@@ -102,6 +102,9 @@ int bounds_default_tile_3d(int nx, int ny, int nz);
 // The 2D kernel that culls states block by block (one wave per element).
 hipError_t launch_bounds_cull_2d(const BoundsArgs& a, hipStream_t stream);
 bool bounds_cull_fits(const BoundsArgs& a);
+// The same for d = 3 (one workgroup per element).
+hipError_t launch_bounds_cull_3d(const BoundsArgs& a, hipStream_t stream);
+bool bounds_cull_fits_3d(const BoundsArgs& a);
 int bounds_tile_count_2d();
 bool bounds_tile_fits_2d(int tile, int nx, int ny);
 int mixed_tile_count();

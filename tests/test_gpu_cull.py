@@ -128,3 +128,50 @@ def test_bad_rows_and_states(kbl, monkeypatch):
     assert np.array_equal(s, t) and (s != 0).any() and (s == 0).any()
     assert np.array_equal(np.isnan(b), np.isnan(c))
     np.testing.assert_allclose(b, c, rtol=1e-11, atol=1e-11)
+
+
+# d = 3 (tile 9): block sizes 4 and 8 with remainders, several rounds of 256
+# blocks, stencils at and above the staged states (256), no internal energy
+CULL3 = 9
+
+
+def hex_wl(n, p=1, N=3, elems=None, **kw):
+    wl = synth.make_hex_workload(N=N, p=p, grid_nodes=8, name="cull_hex", **kw)
+    wl.grid = GridSpec(GRID_STENCIL, n, k=4.0)
+    if elems:
+        rng = np.random.default_rng(3)
+        wl.cols = np.stack([np.concatenate([[e], rng.choice(np.delete(np.arange(wl.n_elem), e),
+                                                            elems - 1, replace=False)])
+                            for e in range(wl.n_elem)]).astype(np.int32).ravel()
+        wl.rowptr = np.arange(0, wl.n_elem * elems + 1, elems).astype(np.int32)
+    return wl
+
+
+@pytest.mark.parametrize("n,kw", [((2, 2, 2), {}), ((4, 5, 3), {}), ((17, 20, 18), {}),
+                                  ((31, 32, 5), {}), ((33, 9, 10), {}), ((24, 6, 40), {}),
+                                  ((28, 28, 28), {}), ((9, 64, 12), {}),
+                                  ((18, 12, 10), dict(elems=1)),
+                                  ((18, 12, 10), dict(p=2, elems=9)),
+                                  ((18, 12, 10), dict(p=2, elems=10)),
+                                  ((20, 9, 9), dict(gamma=5.0 / 3.0, r_fac=0.0))])
+def test_3d_edges(kbl, monkeypatch, n, kw):
+    wl = hex_wl(n, seed=880 + n[0], **kw)
+    print(f"[cull] hex {n} {kw}", flush=True)
+    b, s = run(kbl, monkeypatch, wl, CULL3)
+    rb, rs = oracle.workload_bounds(wl)
+    assert np.array_equal(s, rs)
+    err, _ = bounds_error(b, rb, 3, stencil_momentum_scale(wl))
+    print(f"[cull] err {err:.2e}", flush=True)
+    assert err <= TOL
+    for blocks in (1, 5, -2):
+        c, t = run(kbl, monkeypatch, wl, CULL3, blocks)
+        assert np.array_equal(b.view(np.uint8), c.view(np.uint8)) and np.array_equal(s, t)
+
+
+def test_3d_ties(kbl, monkeypatch):
+    wl = hex_wl((18, 18, 18), seed=890)
+    wl.states = np.array([1.3, 0.4, -0.2, 0.1, 2.1])[:, None] * np.ones_like(wl.states)
+    b, s = run(kbl, monkeypatch, wl, CULL3)
+    rb, rs = oracle.workload_bounds(wl)
+    assert np.array_equal(s, rs)
+    assert bounds_error(b, rb, 3, stencil_momentum_scale(wl))[0] <= TOL
