@@ -32,15 +32,13 @@ __device__ __forceinline__ bool finite_bits(double x) {
     return (__double_as_longlong(x) & 0x7ff0000000000000LL) != 0x7ff0000000000000LL;
 }
 
+// Primitive variables and admissibility of a conserved state (my = mz = 0
+// past the dimension).
 template <int D>
-__device__ __forceinline__ Prim load_prim(const BoundsArgs& p, int64_t node) {
+__device__ __forceinline__ Prim make_prim(const BoundsArgs& p, double rho, double mx, double my,
+                                          double mz, double E) {
     static_assert(D >= 1 && D <= 3, "d = 1, 2 or 3");
     Prim s;
-    const double rho = p.states[node];
-    const double mx = p.states[p.n_nodes + node];
-    const double my = (D >= 2) ? p.states[2 * p.n_nodes + node] : 0.0;
-    const double mz = (D == 3) ? p.states[3 * p.n_nodes + node] : 0.0;
-    const double E = p.states[(D + 1) * p.n_nodes + node];
     double mm, P;
     {
 #pragma clang fp contract(off)
@@ -57,6 +55,16 @@ __device__ __forceinline__ Prim load_prim(const BoundsArgs& p, int64_t node) {
     s.ok = finite_bits(rho) && finite_bits(mx) && finite_bits(my) && finite_bits(mz) &&
            finite_bits(E) && finite_bits(P) && finite_bits(s.th) && rho > 0.0 && P > 0.0;
     return s;
+}
+
+template <int D>
+__device__ __forceinline__ Prim load_prim(const BoundsArgs& p, int64_t node) {
+    const double rho = p.states[node];
+    const double mx = p.states[p.n_nodes + node];
+    const double my = (D >= 2) ? p.states[2 * p.n_nodes + node] : 0.0;
+    const double mz = (D == 3) ? p.states[3 * p.n_nodes + node] : 0.0;
+    const double E = p.states[(D + 1) * p.n_nodes + node];
+    return make_prim<D>(p, rho, mx, my, mz, E);
 }
 
 // Wave64 reductions on the lane networks (no LDS round trips): DPP inside
@@ -249,9 +257,8 @@ struct ExpPrep {
     double q;
     int ni;
 };
-__device__ __forceinline__ ExpPrep exp_prep(double x) {
+__device__ __forceinline__ ExpPrep exp_prep_clamped(double x) {
     constexpr double kInvStep = 0x1.71547652b82fep+8;   // 256 / ln 2
-    x = fmax(x, -1100.0);
     const double t = fma(x, kInvStep, 0x1.8p52);
     const double n = t - 0x1.8p52;
     ExpPrep e;
@@ -264,6 +271,7 @@ __device__ __forceinline__ ExpPrep exp_prep(double x) {
     e.q = r * q;
     return e;
 }
+__device__ __forceinline__ ExpPrep exp_prep(double x) { return exp_prep_clamped(fmax(x, -1100.0)); }
 __device__ __forceinline__ double exp_fin(const ExpPrep& e, const ExpPair& T) {
     return ldexp(fma(T.t24, e.q, T.t), e.ni >> 8);
 }

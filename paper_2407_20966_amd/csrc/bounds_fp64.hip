@@ -688,114 +688,6 @@ __global__ __launch_bounds__(NT) void bounds_fp64_1d_energy(BoundsArgs p) {
     }
 }
 
-// ---------------------------------------------------------------- 1D kernel
-// No separability to exploit: each pair costs sub, mul and two fma before the
-// four min/max.  Coefficients are broadcast from LDS.
-// Up to 8 nodes per thread, three waves per SIMD are required of the register
-// allocation (168 VGPRs): at T = 8 the compiler then keeps a few
-// element-invariant values in scratch, reloaded outside the state loop, and
-// small launches (one-dimensional meshes of a few thousand elements) run
-// 7% faster than at two waves per SIMD; four waves would spill too much.
-template <int NT, int T>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(T <= 8 ? 3 : 1)))
-void bounds_fp64_1d(BoundsArgs p) {
-    __shared__ Coef sC[kMaxStates];
-    __shared__ ExpPair sExp[256];
-    __shared__ Red red;
-    const int tid = threadIdx.x;
-    const double rm = 1.0 - p.r_fac, rp = 1.0 + p.r_fac;
-    stage_exp_table<NT>(sExp);   // published by the prologue's barriers
-    for (ElemRange er = xcd_range(p.n_elem, p.grid_blocks); er.e < er.end; er.e += er.step) {
-        const int64_t e = er.e;
-        const int64_t row0 = p.rowptr[e], row1 = p.rowptr[e + 1];
-        if (row0 < 0 || row1 <= row0 || row1 > p.nnz) {
-            if (tid == 0) store_nan<1>(p, e, KBL_ST_BAD_STENCIL);
-            continue;
-        }
-        const int64_t S = (row1 - row0) * p.n_s;
-        double box[4];
-        const uint32_t flags = stencil_prologue<1, NT>(p, row0, S, red, sC, box);
-        if (flags & (KBL_ST_BAD_STENCIL | KBL_ST_INADMISSIBLE)) {
-            if (tid == 0) store_nan<1>(p, e, flags);
-            continue;
-        }
-        const double lo = box[0];
-        const double h = (box[1] - box[0]) / (double)(p.nx - 1);
-        // no +-inf starting values: the stencil's first state sets the
-        // envelopes (the empty asm gives the registers a defined value)
-        double u[T], qtn[T], qtx[T], qin[T], qix[T];
-#pragma unroll
-        for (int i = 0; i < T; ++i) {
-            const int j = tid + NT * i;
-            u[i] = node_pos(lo, j < p.nx ? j : p.nx - 1, h);
-            asm volatile("" : "=v"(qtn[i]), "=v"(qtx[i]), "=v"(qin[i]), "=v"(qix[i]));
-        }
-        for (int64_t c0 = 0; c0 < S; c0 += kMaxStates) {
-            const int cn = (int)((S - c0) < kMaxStates ? (S - c0) : kMaxStates);
-            if (c0 > 0) stage_chunk<1, NT>(p, row0, c0, cn, sC);
-            int s0 = 0;
-            if (c0 == 0) {
-                const Coef c = sC[0];
-#pragma unroll
-                for (int i = 0; i < T; ++i) {
-                    const double d = u[i] - c.ux;
-                    const double t = c.nk * d;
-                    const double q = fma(t, d, c.a);
-                    const double qi = fma(t, d, c.al);
-                    qtn[i] = q;
-                    qtx[i] = q;
-                    qin[i] = qi;
-                    qix[i] = qi;
-                }
-                s0 = 1;
-            }
-            for (int s = s0; s < cn; ++s) {
-                const Coef c = sC[s];
-#pragma unroll
-                for (int i = 0; i < T; ++i) {
-                    const double d = u[i] - c.ux;
-                    const double t = c.nk * d;
-                    const double q = fma(t, d, c.a);
-                    const double qi = fma(t, d, c.al);
-                    qtn[i] = fmin(qtn[i], q);
-                    qtx[i] = fmax(qtx[i], q);
-                    qin[i] = fmin(qin[i], qi);
-                    qix[i] = fmax(qix[i], qi);
-                }
-            }
-        }
-        // unrelaxed envelope sums, relaxed once per thread afterwards; the
-        // momentum sums split M u by sign (as in the 2D kernel)
-        double sr[2] = {0, 0}, se[2] = {0, 0}, mn[2] = {0, 0}, mx[2] = {0, 0};
-#pragma unroll
-        for (int i = 0; i < T; ++i) {
-            const int j = tid + NT * i;
-            if (j >= p.nx) continue;
-            const double M = h * ((j == 0 || j == p.nx - 1) ? 0.5 : 1.0);
-            const double gtn = exp_tab(qtn[i], sExp);
-            const double gtx = exp_tab(qtx[i], sExp);
-            const double gin = exp_tab(qin[i], sExp);
-            const double gix = exp_tab(qix[i], sExp);
-            const double hu2 = 0.5 * u[i] * u[i];
-            sr[0] += M * gtn;
-            sr[1] += M * gtx;
-            se[0] += M * (hu2 * gtn + gin);
-            se[1] += M * (hu2 * gtx + gix);
-            const double mu = M * u[i];
-            const double neg = fmin(mu, 0.0), pos = fmax(mu, 0.0);
-            mn[0] += neg * gtx;
-            mn[1] += pos * gtn;
-            mx[0] += neg * gtn;
-            mx[1] += pos * gtx;
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        double part[8] = {rm * sr[0], rp * sr[1], rm * se[0], rp * se[1],
-                          rp * mn[0] + rm * mn[1], rm * mx[0] + rp * mx[1], 0.0, 0.0};
-        const double sum = block_sum8<NT>(part, red);
-        if (tid < 6) store_bound_value<1>(p, e, tid, sum, flags);
-    }
-}
-
 template <typename K>
 hipError_t launch(K kernel, int threads, const BoundsArgs& a, hipStream_t stream) {
     hipLaunchKernelGGL(kernel, dim3(bounds_grid(a)), dim3(threads), 0, stream, a);
@@ -838,7 +730,6 @@ constexpr Tile2D kTiles2D[] = {
     KBL_TILE(16, 16, 4, 4, 3),   // 14: n <= 64, states culled block by block
 };
 #undef KBL_TILE
-constexpr int kCullTile = 14;
 constexpr int kNumTiles2D = sizeof(kTiles2D) / sizeof(kTiles2D[0]);
 
 // Defaults from a measured sweep: with A, A + l and B read from LDS tables
@@ -912,13 +803,7 @@ hipError_t launch_bounds_fp64(const BoundsArgs& a, int dim, hipStream_t stream, 
         if (!bounds_tile_fits_2d(tile, a.nx, a.ny)) return hipErrorInvalidValue;
         return kTiles2D[tile].fn(a, stream);
     }
-    if (a.nx <= 64) return launch(bounds_fp64_1d<64, 1>, 64, a, stream);
-    if (a.nx <= 256) return launch(bounds_fp64_1d<256, 1>, kThreads, a, stream);
-    if (a.nx <= 512) return launch(bounds_fp64_1d<256, 2>, kThreads, a, stream);
-    if (a.nx <= 1024) return launch(bounds_fp64_1d<256, 4>, kThreads, a, stream);
-    if (a.nx <= 2048) return launch(bounds_fp64_1d<256, 8>, kThreads, a, stream);
-    if (a.nx <= 4096) return launch(bounds_fp64_1d<256, 16>, kThreads, a, stream);
-    return hipErrorInvalidValue;
+    return launch_bounds_fp64_1d(a, stream);
 }
 
 }  // namespace kbl

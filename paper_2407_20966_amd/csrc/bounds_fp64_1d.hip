@@ -1,0 +1,85 @@
+// FP64 kinetic bounds over a one-dimensional velocity grid (steps 1-3 of the
+// overview in Sec. 3.9), gfx950: the method of bounds_fp64.hip without the
+// separable tables.
+#include "bounds_1d.h"
+
+namespace kbl {
+namespace {
+
+// One workgroup per element; the nodes go in rounds of NT T (thread t owns
+// nodes t + NT i of a round).
+// What bounds it: VALU issue, 8 ops per (state, node) and 77 per node for the
+// four exps and the moments.  Two nodes per thread and round and at most 96
+// VGPRs keep five waves on a SIMD to cover the prologue, the exp table reads
+// and the barriers: 20000 stencils of 12 states take 249 us with 2048 nodes,
+// 140 with 1000 and 108 with 500 (290, 171 and 118 with all of a thread's
+// nodes at once, in up to 168 VGPRs; four nodes per round, four waves: 254,
+// 145, 159); 30000 with 200 nodes take 125 us against 144.
+template <int NT, int T>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(5)))
+void bounds_fp64_1d(BoundsArgs p) {
+    __shared__ Coef sC[kMaxStates];
+    __shared__ ExpPair sExp[256];
+    __shared__ Red red;
+    const int tid = threadIdx.x;
+    const double rm = 1.0 - p.r_fac, rp = 1.0 + p.r_fac;
+    stage_exp_table<NT>(sExp);   // published by the prologue's barriers
+    for (ElemRange er = xcd_range(p.n_elem, p.grid_blocks); er.e < er.end; er.e += er.step) {
+        const int64_t e = er.e;
+        const int64_t row0 = p.rowptr[e], row1 = p.rowptr[e + 1];
+        if (row0 < 0 || row1 <= row0 || row1 > p.nnz) {
+            if (tid == 0) store_nan<1>(p, e, KBL_ST_BAD_STENCIL);
+            continue;
+        }
+        const int64_t S = (row1 - row0) * p.n_s;
+        double box[4];
+        const uint32_t flags = stencil_prologue<1, NT>(p, row0, S, red, sC, box);
+        if (flags & (KBL_ST_BAD_STENCIL | KBL_ST_INADMISSIBLE)) {
+            if (tid == 0) store_nan<1>(p, e, flags);
+            continue;
+        }
+        const double lo = box[0];
+        const double h = (box[1] - box[0]) / (double)(p.nx - 1);
+        Sums1D sum1;
+        if (S <= kMaxStates) {
+            for (int j0 = 0; j0 < p.nx; j0 += NT * T) {
+                Env1D<T> env;
+                env.fold(p, sC, (int)S, lo, h, j0 + tid, NT, true);
+                env.contract(p, lo, h, j0 + tid, NT, sExp, sum1);
+            }
+        } else {
+            // chunks of states, staged again in every round; one node per
+            // thread keeps the registers of the staging's logs out of the
+            // way of the branch above
+            for (int j0 = 0; j0 < p.nx; j0 += NT) {
+                Env1D<1> env;
+                for (int64_t c0 = 0; c0 < S; c0 += kMaxStates) {
+                    const int cn = (int)((S - c0) < kMaxStates ? (S - c0) : kMaxStates);
+                    stage_chunk<1, NT>(p, row0, c0, cn, sC);
+                    env.fold(p, sC, cn, lo, h, j0 + tid, NT, c0 == 0);
+                }
+                env.contract(p, lo, h, j0 + tid, NT, sExp, sum1);
+            }
+        }
+        double part[8];
+        sum1.parts(rm, rp, part);
+        const double sum = block_sum8<NT>(part, red);
+        if (tid < 6) store_bound_value<1>(p, e, tid, sum, flags);
+    }
+}
+
+template <int NT, int T>
+hipError_t launch_1d(const BoundsArgs& a, hipStream_t stream) {
+    hipLaunchKernelGGL((bounds_fp64_1d<NT, T>), dim3(bounds_grid(a)), dim3(NT), 0, stream, a);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_bounds_fp64_1d(const BoundsArgs& a, hipStream_t stream) {
+    if (a.nx <= 64) return launch_1d<64, 1>(a, stream);
+    if (a.nx <= 256) return launch_1d<256, 1>(a, stream);
+    return launch_1d<256, 2>(a, stream);
+}
+
+}  // namespace kbl

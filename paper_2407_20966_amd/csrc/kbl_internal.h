@@ -88,10 +88,17 @@ struct RiemannArgs {
     double gm1;
 };
 
+// The velocity grid, gas and limiter parameters of the 1D entry points as kernel
+// arguments (checked as those do; no elements, no pointers).
+kbl_status make_bounds_args_1d(const kbl_params* params, const kbl_vgrid* vgrid, BoundsArgs* a);
+kbl_status make_limit_args_1d(const kbl_params* params, int32_t n_s, const double* node_weights,
+                              LimitArgs* a);
+
 // Host-side launchers (one per translation unit).  They return hipSuccess or
 // the launch error; argument checking happened before.
 // tile < 0 selects the default 2D tile for the grid size.
 hipError_t launch_bounds_fp64(const BoundsArgs& a, int dim, hipStream_t stream, int tile);
+hipError_t launch_bounds_fp64_1d(const BoundsArgs& a, hipStream_t stream);
 // Energy bounds from the per-state integrand (KBL_FLAG_ENERGY_PERSTATE).
 hipError_t launch_bounds_fp64_energy(const BoundsArgs& a, int dim, hipStream_t stream);
 // d = 3: FP64 bounds over a 3D velocity grid (tile < 0: default for the grid).
