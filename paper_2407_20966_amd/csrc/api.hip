@@ -234,6 +234,19 @@ kbl_status scratch_address(void** out) {
 
 }  // namespace
 
+namespace kbl {
+
+kbl_status make_bounds_args_1d(const kbl_params* params, const kbl_vgrid* vgrid, BoundsArgs* a) {
+    return make_bounds_args(params, 1, 0, 0, 1, 0, nullptr, nullptr, nullptr, vgrid, kMax1DNodes, a);
+}
+
+kbl_status make_limit_args_1d(const kbl_params* params, int32_t n_s, const double* node_weights,
+                              LimitArgs* a) {
+    return make_limit_args(params, 1, 0, n_s, node_weights, a);
+}
+
+}  // namespace kbl
+
 extern "C" {
 
 void kbl_default_params(kbl_params* p, double gamma) {

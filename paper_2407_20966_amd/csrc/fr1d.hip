@@ -12,25 +12,24 @@
 //    scheme stays exactly conservative.
 //  - fr1d_stage<P>: the Shu-Osher stage combination, then the end values of
 //    the new solution and the ghost elements.
-//  - fr1d_csr: the node stencils of the bounds (constant per mesh).
+//  - fr1d_csr: the node stencils of the initial limiting.
 //  - fr1d_max_speed: max |u| + c over the solution points.
-// The bounds and the limiter are the library's own entry points
+// A limited stage follows the overview of Sec. 3.9 (bounds from the stage's
+// input state, the update, then the limiting of the updated state into those
+// bounds) in one kernel, fr1d_stage.hip, three launches per step; fr1d_rhs and
+// fr1d_stage serve the residual entry point and steps without limiting.  The
+// initial limiting uses the library's own entry points
 // (kbl_compute_bounds_nodes, kbl_limit) on the node layout of kbl_fr1d.h.
-// Every stage follows the overview of Sec. 3.9: bounds from the stage's
-// input state, the update, then the limiting of the updated state into
-// those bounds.
 #include <math.h>
 #include <string.h>
 
-#include <algorithm>
 
-#include "../../include/kbl_fr1d.h"
-#include "kbl_internal.h"
+#include "fr1d_internal.h"
 
 namespace kbl {
 namespace {
 
-constexpr int kMaxNs = KBL_FR_MAX_DEGREE + 1;
+constexpr int kMaxNs = kFrNs;
 constexpr int kThreadsFr = 256;
 
 // Element operators on the reference element [-1, 1].
@@ -66,50 +65,6 @@ __device__ __forceinline__ double interp(const double* at, const double* u) {
 #pragma unroll
     for (int j = 1; j < NS; ++j) s = fma(at[j], u[j], s);
     return s;
-}
-
-__device__ __forceinline__ void euler_flux(double gm1, const double w[3], double f[3]) {
-#pragma clang fp contract(off)
-    const double u = w[1] / w[0];
-    const double P = gm1 * (w[2] - 0.5 * w[1] * u);
-    f[0] = w[1];
-    f[1] = w[1] * u + P;
-    f[2] = (w[2] + P) * u;
-}
-
-// HLLC flux (Toro, Spruce and Speares) with the speeds
-// S_L = min(u_L - c_L, u_R - c_R), S_R = max(u_L + c_L, u_R + c_R).
-__device__ __forceinline__ void hllc(double gamma, double gm1, const double L[3], const double Rr[3],
-                                     double F[3]) {
-#pragma clang fp contract(off)
-    const double ul = L[1] / L[0], ur = Rr[1] / Rr[0];
-    const double pl = gm1 * (L[2] - 0.5 * L[1] * ul);
-    const double pr = gm1 * (Rr[2] - 0.5 * Rr[1] * ur);
-    const double cl = sqrt(gamma * pl / L[0]), cr = sqrt(gamma * pr / Rr[0]);
-    const double SL = fmin(ul - cl, ur - cr);
-    const double SR = fmax(ul + cl, ur + cr);
-    const double dl = L[0] * (SL - ul), dr = Rr[0] * (SR - ur);
-    const double Ss = (pr - pl + ul * dl - ur * dr) / (dl - dr);
-    double fl[3], fr[3];
-    euler_flux(gm1, L, fl);
-    euler_flux(gm1, Rr, fr);
-    if (0.0 <= SL) {
-        F[0] = fl[0]; F[1] = fl[1]; F[2] = fl[2];
-    } else if (0.0 <= Ss) {
-        const double k = dl / (SL - Ss);
-        const double e = k * (L[2] / L[0] + (Ss - ul) * (Ss + pl / dl));
-        F[0] = fl[0] + SL * (k - L[0]);
-        F[1] = fl[1] + SL * (k * Ss - L[1]);
-        F[2] = fl[2] + SL * (e - L[2]);
-    } else if (0.0 <= SR) {
-        const double k = dr / (SR - Ss);
-        const double e = k * (Rr[2] / Rr[0] + (Ss - ur) * (Ss + pr / dr));
-        F[0] = fr[0] + SR * (k - Rr[0]);
-        F[1] = fr[1] + SR * (k * Ss - Rr[1]);
-        F[2] = fr[2] + SR * (e - Rr[2]);
-    } else {
-        F[0] = fr[0]; F[1] = fr[1]; F[2] = fr[2];
-    }
 }
 
 template <int NS>
@@ -156,15 +111,15 @@ __global__ __launch_bounds__(kThreadsFr) void fr1d_rhs(FrArgs a) {
         for (int v = 0; v < 3; ++v) nr[v] = a.right[v];
     }
     double Fs_l[3], Fs_r[3];
-    hllc(a.gamma, a.gm1, nl, uL, Fs_l);
-    hllc(a.gamma, a.gm1, uR, nr, Fs_r);
+    fr_hllc(a.gamma, a.gm1, nl, uL, Fs_l);
+    fr_hllc(a.gamma, a.gm1, uR, nr, Fs_r);
     // point fluxes and their interpolants at the ends
     double F[3][NS];
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
         const double w[3] = {u[0][j], u[1][j], u[2][j]};
         double f[3];
-        euler_flux(a.gm1, w, f);
+        fr_euler_flux(a.gm1, w, f);
         F[0][j] = f[0]; F[1][j] = f[1]; F[2][j] = f[2];
     }
 #pragma unroll
@@ -220,17 +175,15 @@ __global__ __launch_bounds__(kThreadsFr) void fr1d_stage(FrArgs a) {
     }
 }
 
-// Node stencils.  Stage stencil (Sec. 5): row e < n_elem lists the
-// element's n_v nodes and the neighbours' end values on the shared faces.
-// Initial stencil: the solution points of the element and of its two face
-// neighbours.  Ghost rows list their own nodes.
+// Node stencils of the initial limiting: the solution points of the element
+// and of its two face neighbours.  Ghost rows list their own nodes.
 __global__ __launch_bounds__(kThreadsFr) void fr1d_csr(int64_t n_elem, int64_t n_tot, int32_t n_v,
-                                                       int32_t bc, int32_t initial, int32_t* rowptr,
+                                                       int32_t bc, int32_t* rowptr,
                                                        int32_t* cols) {
     const int64_t r = (int64_t)blockIdx.x * kThreadsFr + threadIdx.x;
     if (r >= n_tot) return;
     const int32_t ns = n_v - 2;
-    const int64_t row_len = initial ? 3 * ns : n_v + 2;
+    const int64_t row_len = 3 * ns;
     const int64_t start = r < n_elem ? r * row_len : n_elem * row_len + (r - n_elem) * n_v;
     int64_t len = n_v;
     if (r < n_elem) {
@@ -242,15 +195,9 @@ __global__ __launch_bounds__(kThreadsFr) void fr1d_csr(int64_t n_elem, int64_t n
             lnb = r > 0 ? r - 1 : n_elem;
             rnb = r < n_elem - 1 ? r + 1 : n_elem + 1;
         }
-        if (initial) {
-            const int64_t q[3] = {r, lnb, rnb};
-            for (int i = 0; i < 3; ++i)
-                for (int j = 0; j < ns; ++j) cols[start + i * ns + j] = (int32_t)(q[i] * n_v + j);
-        } else {
-            for (int j = 0; j < n_v; ++j) cols[start + j] = (int32_t)(r * n_v + j);
-            cols[start + n_v] = (int32_t)(lnb * n_v + ns + 1);      // left neighbour's right end
-            cols[start + n_v + 1] = (int32_t)(rnb * n_v + ns);      // right neighbour's left end
-        }
+        const int64_t q[3] = {r, lnb, rnb};
+        for (int i = 0; i < 3; ++i)
+            for (int j = 0; j < ns; ++j) cols[start + i * ns + j] = (int32_t)(q[i] * n_v + j);
         len = row_len;
     } else {
         for (int j = 0; j < n_v; ++j) cols[start + j] = (int32_t)(r * n_v + j);
@@ -416,14 +363,15 @@ bool valid_cfg(const kbl_fr1d* c) {
 
 int64_t n_total(const kbl_fr1d* c) { return c->n_elem + (c->bc == KBL_FR_DIRICHLET ? 2 : 0); }
 
-int64_t stencil_nnz(const kbl_fr1d* c, bool initial) {
-    const int64_t nv = c->p + 3;
-    const int64_t row = initial ? 3 * (c->p + 1) : nv + 2;
-    return c->n_elem * row + (n_total(c) - c->n_elem) * nv;
+int64_t stencil_nnz(const kbl_fr1d* c) {
+    return c->n_elem * 3 * (c->p + 1) + (n_total(c) - c->n_elem) * (c->p + 3);
 }
 
 size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// Workspace.  A limited step keeps the outputs of its first two stages there,
+// both [3][n_elem * n_v]: the first in U0, the second from R on (R and bounds
+// are adjacent and hold 3 n_elem (p + 1) + 6 n_tot >= 3 n_elem (p + 3) values).
 struct Ws {
     double* U0;
     double* R;
@@ -443,8 +391,7 @@ size_t ws_layout(const kbl_fr1d* c, char* base, Ws* w) {
     t.bounds = (double*)take(6 * (size_t)nt * 8);
     t.bstat = (uint32_t*)take((size_t)nt * 4);
     t.rowptr = (int32_t*)take((size_t)(nt + 1) * 4);
-    const int64_t nnz = std::max(stencil_nnz(c, false), stencil_nnz(c, true));
-    t.cols = (int32_t*)take((size_t)nnz * 4);
+    t.cols = (int32_t*)take((size_t)stencil_nnz(c) * 4);
     if (w) *w = t;
     return off;
 }
@@ -503,28 +450,11 @@ hipError_t launch_stage(const FrArgs& a, int p, hipStream_t st) {
     return hipGetLastError();
 }
 
-// Bounds of the node stencils of the current state (steps 1-3 of Sec. 3.9).
-kbl_status stencil_bounds(const kbl_fr1d* c, const kbl_params* params, const kbl_vgrid* vgrid,
-                          const FrArgs& a, const Ws& ws, bool initial, hipStream_t st) {
-    return kbl_compute_bounds_nodes(params, 1, a.n_tot, a.cols, stencil_nnz(c, initial), a.U,
-                                    ws.rowptr, ws.cols, vgrid, ws.bounds, ws.bstat, st);
-}
-
-// Squeeze limiter and pressure step of the current state over V into the
-// bounds in the workspace (steps 5-7 of Sec. 3.9; end values weight 0).
-kbl_status limit_into(const kbl_fr1d* c, const kbl_params* params, const FrArgs& a, const Ws& ws,
-                      const double* w, uint32_t* elem_status, hipStream_t st) {
-    double cw[kMaxNs + 2];
-    for (int j = 0; j < c->p + 1; ++j) cw[j] = w[j];
-    cw[c->p + 1] = 0.0;
-    cw[c->p + 2] = 0.0;
-    return kbl_limit(params, 1, a.n_tot, a.n_v, a.U, ws.bounds, cw, a.U, nullptr, elem_status, st);
-}
-
-hipError_t launch_csr(const FrArgs& a, const Ws& ws, bool initial, hipStream_t st) {
-    hipLaunchKernelGGL(fr1d_csr, dim3(blocks_for(a.n_tot)), dim3(kThreadsFr), 0, st, a.n_elem,
-                       a.n_tot, a.n_v, a.bc, initial ? 1 : 0, ws.rowptr, ws.cols);
-    return hipGetLastError();
+// Mean weights over V: the quadrature weights, end values weight 0.
+void mean_weights(int p, const double* w, double* cw) {
+    for (int j = 0; j < p + 1; ++j) cw[j] = w[j];
+    cw[p + 1] = 0.0;
+    cw[p + 2] = 0.0;
 }
 
 // Checks shared by the limiting entry points (before any launch).
@@ -582,19 +512,59 @@ kbl_status kbl_fr1d_limit(const kbl_fr1d* cfg, const kbl_params* params, const k
     a.b = 0.0;   // end values and ghosts only
     if (kbl::launch_stage(a, cfg->p, st) != hipSuccess) return KBL_ERR_HIP;
     if (!cfg->limit) return KBL_OK;
-    if (kbl::launch_csr(a, ws, true, st) != hipSuccess) return KBL_ERR_HIP;
-    rc = kbl::stencil_bounds(cfg, params, vgrid, a, ws, true, st);
+    hipLaunchKernelGGL(kbl::fr1d_csr, dim3(kbl::blocks_for(a.n_tot)), dim3(kbl::kThreadsFr), 0, st,
+                       a.n_elem, a.n_tot, a.n_v, a.bc, ws.rowptr, ws.cols);
+    if (hipGetLastError() != hipSuccess) return KBL_ERR_HIP;
+    rc = kbl_compute_bounds_nodes(params, 1, a.n_tot, a.cols, kbl::stencil_nnz(cfg), a.U, ws.rowptr,
+                                  ws.cols, vgrid, ws.bounds, ws.bstat, st);
     if (rc != KBL_OK) return rc;
     hipLaunchKernelGGL(kbl::fr1d_keep_admissible, dim3(kbl::blocks_for(a.n_tot)),
                        dim3(kbl::kThreadsFr), 0, st, a.U, a.n_tot, a.cols, a.n_v, a.gm1, ws.bounds);
     if (hipGetLastError() != hipSuccess) return KBL_ERR_HIP;
-    return kbl::limit_into(cfg, params, a, ws, w, elem_status, st);
+    double cw[kbl::kMaxNs + 2];
+    kbl::mean_weights(cfg->p, w, cw);
+    return kbl_limit(params, 1, a.n_tot, a.n_v, a.U, ws.bounds, cw, a.U, nullptr, elem_status, st);
 }
 
 }  // extern "C"
 
 namespace kbl {
 namespace {
+
+// Arguments of the limited stages shared by the three of a step.
+kbl_status make_stage_args(const kbl_fr1d* c, const kbl_params* params, const kbl_vgrid* vgrid,
+                           const FrArgs& a, const double* w, FrStageArgs* f) {
+    memset(f, 0, sizeof(*f));
+    kbl_status rc = make_bounds_args_1d(params, vgrid, &f->b);
+    if (rc != KBL_OK) return rc;
+    double cw[kMaxNs + 2];
+    mean_weights(c->p, w, cw);
+    rc = make_limit_args_1d(params, a.n_v, cw, &f->l);
+    if (rc != KBL_OK) return rc;
+    f->U0 = a.U;
+    f->u0_stride = a.cols;
+    f->n_elem = a.n_elem;
+    f->n_s = a.n_v - 2;
+    f->n_v = a.n_v;
+    f->bc = a.bc;
+    f->inv_jac = a.inv_jac;
+    f->lhd = f->b.half_delta > 0.0 ? log(f->b.half_delta / (2.0 * kPi)) : 0.0;
+    f->gamma = a.gamma;
+    f->gm1 = a.gm1;
+    for (int v = 0; v < 3; ++v) {
+        f->left[v] = a.left[v];
+        f->right[v] = a.right[v];
+    }
+    const int ns = f->n_s;
+    for (int j = 0; j < ns; ++j) {
+        f->at[0][j] = a.ops.at_m1[j];
+        f->at[1][j] = a.ops.at_p1[j];
+        f->dg[0][j] = a.ops.dgL[j];
+        f->dg[1][j] = a.ops.dgR[j];
+        for (int k = 0; k < ns; ++k) f->D[j][k] = a.ops.D[j * ns + k];
+    }
+    return KBL_OK;
+}
 
 // One SSP-RK3 step; dt from the argument, or from tdt[1] in device memory.
 kbl_status step_impl(const kbl_fr1d* cfg, const kbl_params* params, const kbl_vgrid* vgrid,
@@ -610,36 +580,46 @@ kbl_status step_impl(const kbl_fr1d* cfg, const kbl_params* params, const kbl_vg
     kbl::Ws ws;
     kbl::ws_layout(cfg, (char*)workspace, &ws);
     hipStream_t st = (hipStream_t)stream;
-    a.U0 = ws.U0;
-    a.R = ws.R;
-    a.dt = dt;
-    a.tdt = tdt;
-    if (cfg->limit) {
-        if (kbl::launch_csr(a, ws, false, st) != hipSuccess) return KBL_ERR_HIP;
-        // end values and ghosts of the input state (its bounds need them)
-        a.a = 1.0;
-        a.b = 0.0;
-        if (kbl::launch_stage(a, cfg->p, st) != hipSuccess) return KBL_ERR_HIP;
-    }
     // Shu-Osher SSP-RK3: u1 = u + dt L(u); u2 = 3/4 u + 1/4 (u1 + dt L(u1));
     // u^{n+1} = 1/3 u + 2/3 (u2 + dt L(u2)).  Each stage: bounds of its input
     // state, update, limiting of the updated state into those bounds.
     const double ca[3] = {0.0, 0.75, 1.0 / 3.0};
     const double cb[3] = {1.0, 0.25, 2.0 / 3.0};
-    for (int s = 0; s < 3; ++s) {
-        if (cfg->limit) {
-            rc = kbl::stencil_bounds(cfg, params, vgrid, a, ws, false, st);
-            if (rc != KBL_OK) return rc;
+    if (cfg->limit) {
+        kbl::FrStageArgs f;
+        rc = kbl::make_stage_args(cfg, params, vgrid, a, w, &f);
+        if (rc != KBL_OK) return rc;
+        f.dt = dt;
+        f.tdt = tdt;
+        const double* src = U;
+        double* dst[3] = {ws.U0, ws.R, U};
+        for (int s = 0; s < 3; ++s) {
+            const int64_t inner = a.n_elem * a.n_v;   // columns of the workspace's states
+            f.A = src;
+            f.a_stride = s == 0 ? a.cols : inner;
+            f.B = dst[s];
+            f.b_stride = s == 2 ? a.cols : inner;
+            f.first = s == 0;
+            f.ca = ca[s];
+            f.cb = cb[s];
+            // the ghosts' values and status come from the last stage alone
+            f.n_launch = s == 2 ? a.n_tot : a.n_elem;
+            f.status = s == 2 ? elem_status : nullptr;
+            if (kbl::launch_fr1d_stage_limited(f, st) != hipSuccess) return KBL_ERR_HIP;
+            src = dst[s];
         }
+        return KBL_OK;
+    }
+    a.U0 = ws.U0;
+    a.R = ws.R;
+    a.dt = dt;
+    a.tdt = tdt;
+    for (int s = 0; s < 3; ++s) {
         if (kbl::launch_rhs(a, cfg->p, st) != hipSuccess) return KBL_ERR_HIP;
         a.a = ca[s];
         a.b = cb[s];
         a.save_u0 = s == 0;
         if (kbl::launch_stage(a, cfg->p, st) != hipSuccess) return KBL_ERR_HIP;
-        if (cfg->limit) {
-            rc = kbl::limit_into(cfg, params, a, ws, w, s == 2 ? elem_status : nullptr, st);
-            if (rc != KBL_OK) return rc;
-        }
     }
     return KBL_OK;
 }
