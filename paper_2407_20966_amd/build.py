@@ -47,6 +47,7 @@ def hipcc() -> str:
 SOURCE_FLAGS = {
     "bounds_fp64.hip": ["-fno-honor-nans"],
     "bounds_fp64_3d.hip": ["-fno-honor-nans"],
+    "bounds_energy.hip": ["-fno-honor-nans", "-mllvm", "-disable-machine-licm"],
     "bounds_fp64_1d.hip": ["-fno-honor-nans", "-mllvm", "-disable-machine-licm"],
     # NaNs reach the fused stage's residual and limiter
     "fr1d_stage.hip": ["-mllvm", "-disable-machine-licm"],
