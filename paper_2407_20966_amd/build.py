@@ -46,6 +46,7 @@ def hipcc() -> str:
 # min/max need no canonicalisation (one VALU op per min/max, not two).
 SOURCE_FLAGS = {
     "bounds_fp64.hip": ["-fno-honor-nans"],
+    "bounds_fp64_small.hip": ["-fno-honor-nans", "-mllvm", "-disable-machine-licm"],
     "bounds_fp64_3d.hip": ["-fno-honor-nans"],
     "bounds_energy.hip": ["-fno-honor-nans", "-mllvm", "-disable-machine-licm"],
     "bounds_fp64_1d.hip": ["-fno-honor-nans", "-mllvm", "-disable-machine-licm"],
