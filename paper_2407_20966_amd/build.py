@@ -44,6 +44,9 @@ def hipcc() -> str:
 # Per-source device flags.  The bounds kernels validate every input before
 # their hot loop, which is then NaN-free: without NaN semantics the running
 # min/max need no canonicalisation (one VALU op per min/max, not two).
+# Machine LICM hoists the materialised constants of the FP64 logs and exps out
+# of the loop over elements and keeps them in registers for the whole kernel;
+# the files whose kernels lose a wave per SIMD to that, or spill, turn it off.
 SOURCE_FLAGS = {
     "bounds_fp64.hip": ["-fno-honor-nans"],
     "bounds_fp64_small.hip": ["-fno-honor-nans", "-mllvm", "-disable-machine-licm"],
@@ -54,12 +57,8 @@ SOURCE_FLAGS = {
     "fr1d_stage.hip": ["-mllvm", "-disable-machine-licm"],
     "bounds_cull_3d.hip": ["-fno-honor-nans", "-mllvm", "-disable-machine-licm"],
     "bounds_cull_2d.hip": ["-fno-honor-nans", "-mllvm", "-disable-machine-licm"],
-    # Machine LICM hoists the materialised constants of the prologue's FP64
-    # log and exp out of the persistent element loop and keeps them in
-    # registers for the whole kernel: without it the 64 x 64 tiles fit two
-    # waves per SIMD instead of one.
     "bounds_mixed.hip": ["-fno-honor-nans", "-mllvm", "-disable-machine-licm"],
-    "backward_fp64.hip": ["-fno-honor-nans"],
+    "backward_fp64.hip": ["-fno-honor-nans", "-mllvm", "-disable-machine-licm"],
 }
 
 

@@ -38,6 +38,15 @@
 //     the extreme states (lo = U - k sqrt(theta), hi = U + k sqrt(theta)).
 //  5. (rho, U, theta) adjoints are mapped to conserved variables and written
 //     to this element's stencil slots.
+// What bounds it: VALU issue at two or three waves per SIMD (registers from
+// 3 x 3 nodes per thread on, the LDS of the per-wave sums below that).  22500
+// quads of 80 states, all listed, on a 48 x 48 grid: about 45 ops per state and
+// thread in the envelopes, 65 per node and envelope for the shares, 120 per
+// winner and envelope.  Forming the winners' moments once per row and column
+// (150 ops per winner before), exps from the table and no machine LICM (whose
+// hoisted constants spilled) took forward and backward there from 2.88 to
+// 2.72 ms, 3600 quads on 64 x 64 nodes from 1.10 to 0.95, 10000 of 45 states on
+// 16 x 16 from 460 to 395 us.
 // A gather kernel then sums, for each node, the slots of listed elements that
 // refer to it, walking the (symmetric) stencil in CSR order.
 #include <type_traits>
@@ -77,21 +86,24 @@ __device__ __forceinline__ double keyed(double v, int s) {
 }
 __device__ __forceinline__ int key_index(double k) { return __double2loint(k) & 0xff; }
 
-// Minimum waves per SIMD the register allocator targets.
-#ifndef KBL_BWD_WAVES
-#define KBL_BWD_WAVES 2
-#endif
+// Minimum waves per SIMD the register allocator targets: 168 VGPRs hold up to
+// four nodes per thread, the larger tiles would spill in their loops.
+constexpr int bwd_waves(int nodes) { return nodes <= 4 ? 3 : 2; }
 
 template <int D, int BX, int BY, int TX, int TY, bool F32>
-__global__ __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(KBL_BWD_WAVES))) void bounds_bwd_fp64(BwdArgs a) {
+__global__ __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(bwd_waves(TX * TY)))) void bounds_bwd_fp64(BwdArgs a) {
     constexpr int NT = BX * BY;
     constexpr int NW = NT / 64;
     static_assert(NT % 64 == 0 && NT <= kThreads, "workgroup must be 1-4 waves");
     static_assert(!F32 || D == 2, "the mixed-precision form is 2D");
+    // exp from the LDS table, unless its 4 KB would cost the third workgroup of
+    // a CU (the small FP64 tiles, whose registers allow it)
+    constexpr bool kTab = F32 || TX * TY > 4;
     __shared__ Coef sC[kMaxStates];
     __shared__ CoefF sF[F32 ? kMaxStates : 1];
     __shared__ double sZw[NW][kMaxStates][5];     // per-wave sums per winning state
     __shared__ int sExt[4];
+    __shared__ ExpPair sExp[kTab ? 256 : 1];
     __shared__ Red red;
 
     const BoundsArgs& p = a.f;
@@ -101,6 +113,7 @@ __global__ __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(KBL_BWD
     const double rm = 1.0 - p.r_fac, rp = 1.0 + p.r_fac;
     const int64_t nslot = p.nnz * p.n_s;
 
+    if (kTab) stage_exp_table<NT>(sExp);   // published by the prologue's barriers
     // only the listed elements: every other element's bounds' adjoint is
     // zero, and so is its contribution (the gather skips its slots)
     const uint32_t n_act = *a.act_count;
@@ -380,7 +393,7 @@ __global__ __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(KBL_BWD
                         const double dy = u[1] - c.uy;
                         qv += (c.nk * dy) * dy;
                     }
-                    const double f = exp(qv);
+                    const double f = kTab ? exp_tab(qv, sExp) : exp(qv);
                     const double wf = M * phi * f;
                     if (p.grid_mode == KBL_GRID_STENCIL && valid) {
                         const int t[2] = {x, y};
@@ -402,10 +415,15 @@ __global__ __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(KBL_BWD
                 const int s = wave_min_i32(lk);
                 if (s == kNoKey) break;
                 const Coef c = sC[s];
-                double z[4] = {0.0, 0.0, 0.0, 0.0};
+                // the shares summed per row and per column of the thread's
+                // nodes, the moments formed once per row and column
+                double zr[TX], zc[TY];
+#pragma unroll
+                for (int j = 0; j < TY; ++j) zc[j] = 0.0;
                 int nlk = kNoKey;
 #pragma unroll
-                for (int i = 0; i < TX; ++i)
+                for (int i = 0; i < TX; ++i) {
+                    zr[i] = 0.0;
 #pragma unroll
                     for (int j = 0; j < TY; ++j) {
                         // the node's share if s won it, selected by a 0/1
@@ -414,12 +432,24 @@ __global__ __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(KBL_BWD
                         const double wf = (m ? 1.0 : 0.0) * wv[i][j];
                         w[i][j] = m ? kNoKey : w[i][j];
                         nlk = min(nlk, w[i][j]);
-                        const double dx = ux[i] - c.ux, dy = D == 2 ? uy[j] - c.uy : 0.0;
-                        const double d2 = dx * dx + dy * dy;
-                        z[0] += wf;
-                        z[1] = fma(wf, dx, z[1]);
-                        if (D == 2) z[2] = fma(wf, dy, z[2]);
-                        z[3] = fma(wf, d2, z[3]);
+                        zr[i] += wf;
+                        if (D == 2) zc[j] += wf;
+                    }
+                }
+                double z[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int i = 0; i < TX; ++i) {
+                    const double dx = ux[i] - c.ux, t = zr[i] * dx;
+                    z[0] += zr[i];
+                    z[1] += t;
+                    z[3] = fma(t, dx, z[3]);
+                }
+                if (D == 2)
+#pragma unroll
+                    for (int j = 0; j < TY; ++j) {
+                        const double dy = uy[j] - c.uy, t = zc[j] * dy;
+                        z[2] += t;
+                        z[3] = fma(t, dy, z[3]);
                     }
                 lk = nlk;
                 double zz[8] = {z[0], z[1], z[2], z[3], internal ? z[0] : 0.0, 0.0, 0.0, 0.0};
