@@ -11,14 +11,16 @@ namespace {
 // BX x BY threads; thread (tx, ty) owns velocity nodes (tx + BX i, ty + BY j),
 // i < TX, j < TY.  BTAB = 1 reads B (and BTAB = 2 also A, A + l) from LDS
 // tables built per sub-chunk of kTabStates states (fewer VALU ops, more LDS
-// traffic and barriers).
-template <int BX, int BY, int TX, int TY, int BTAB>
+// traffic and barriers).  FIT > 0: the threads are split to fit the grid, bx =
+// ceil(nx / TX) by by = ceil(ny / TY), with FIT x FIT tables; the threads left
+// over repeat thread 0 with weight zero.
+template <int BX, int BY, int TX, int TY, int BTAB, int FIT = 0>
 __global__ __launch_bounds__(BX * BY)
-__attribute__((amdgpu_waves_per_eu(BTAB == 2 ? (TX * TY <= 9 ? 3 : 2) : 1))) void bounds_fp64_2d(BoundsArgs p) {
+__attribute__((amdgpu_waves_per_eu(FIT ? 4 : BTAB == 2 ? (TX * TY <= 9 ? 3 : 2) : 1))) void bounds_fp64_2d(BoundsArgs p) {
     constexpr int NT = BX * BY;
-    constexpr int NXM = BX * TX;
-    constexpr int NYM = BY * TY;
-    constexpr int kTabStates = 32;
+    constexpr int NXM = FIT ? FIT : BX * TX;
+    constexpr int NYM = FIT ? FIT : BY * TY;
+    constexpr int kTabStates = FIT ? 16 : 32;
     static_assert(NT % 64 == 0 && NT <= kThreads, "workgroup must be 1-4 waves");
     static_assert(BTAB == 0 || (NXM == NYM && NYM <= NT), "table tiles are square");
     __shared__ Coef sC[kMaxStates];
@@ -29,7 +31,10 @@ __attribute__((amdgpu_waves_per_eu(BTAB == 2 ? (TX * TY <= 9 ? 3 : 2) : 1))) voi
     __shared__ Red red;
 
     const int tid = threadIdx.x;
-    const int tx = tid % BX, ty = tid / BX;
+    const int bx = FIT ? (p.nx + TX - 1) / TX : BX;
+    const int by = FIT ? (p.ny + TY - 1) / TY : BY;
+    const bool idle = FIT && tid >= bx * by;
+    const int tx = idle ? 0 : tid % bx, ty = idle ? 0 : tid / bx;
     const double rm = 1.0 - p.r_fac, rp = 1.0 + p.r_fac;
     stage_exp_table<NT>(sExp);   // published by the prologue's barriers
 
@@ -55,12 +60,12 @@ __attribute__((amdgpu_waves_per_eu(BTAB == 2 ? (TX * TY <= 9 ? 3 : 2) : 1))) voi
         double ux[TX], uy[TY];
 #pragma unroll
         for (int i = 0; i < TX; ++i) {
-            const int j = tx + BX * i;
+            const int j = tx + bx * i;
             ux[i] = node_pos(lox, j < p.nx ? j : p.nx - 1, hx);
         }
 #pragma unroll
         for (int j = 0; j < TY; ++j) {
-            const int jj = ty + BY * j;
+            const int jj = ty + by * j;
             uy[j] = node_pos(loy, jj < p.ny ? jj : p.ny - 1, hy);
         }
 
@@ -124,11 +129,11 @@ __attribute__((amdgpu_waves_per_eu(BTAB == 2 ? (TX * TY <= 9 ? 3 : 2) : 1))) voi
                     double ca[TX], cai[TX], cb[TY];
 #pragma unroll
                     for (int i = 0; i < TX; ++i) {
-                        ca[i] = sA[0][tx + BX * i];
-                        cai[i] = sA[1][tx + BX * i];
+                        ca[i] = sA[0][tx + bx * i];
+                        cai[i] = sA[1][tx + bx * i];
                     }
 #pragma unroll
-                    for (int j = 0; j < TY; ++j) cb[j] = sB[0][ty + BY * j];
+                    for (int j = 0; j < TY; ++j) cb[j] = sB[0][ty + by * j];
                     // The stencil's first state sets the envelopes (q is its
                     // own min and max) instead of comparing with +-inf:
                     // tri2m 152.0 -> 150.6 ms, bounds bitwise the same (v_min
@@ -141,11 +146,11 @@ __attribute__((amdgpu_waves_per_eu(BTAB == 2 ? (TX * TY <= 9 ? 3 : 2) : 1))) voi
                         double na[TX], nai[TX], nb[TY];
 #pragma unroll
                         for (int i = 0; i < TX; ++i) {
-                            na[i] = sA[2 * sn][tx + BX * i];
-                            nai[i] = sA[2 * sn + 1][tx + BX * i];
+                            na[i] = sA[2 * sn][tx + bx * i];
+                            nai[i] = sA[2 * sn + 1][tx + bx * i];
                         }
 #pragma unroll
-                        for (int j = 0; j < TY; ++j) nb[j] = sB[sn][ty + BY * j];
+                        for (int j = 0; j < TY; ++j) nb[j] = sB[sn][ty + by * j];
 #pragma unroll
                         for (int i = 0; i < TX; ++i)
 #pragma unroll
@@ -169,11 +174,11 @@ __attribute__((amdgpu_waves_per_eu(BTAB == 2 ? (TX * TY <= 9 ? 3 : 2) : 1))) voi
                         double na[TX], nai[TX], nb[TY];
 #pragma unroll
                         for (int i = 0; i < TX; ++i) {
-                            na[i] = sA[2 * sn][tx + BX * i];
-                            nai[i] = sA[2 * sn + 1][tx + BX * i];
+                            na[i] = sA[2 * sn][tx + bx * i];
+                            nai[i] = sA[2 * sn + 1][tx + bx * i];
                         }
 #pragma unroll
-                        for (int j = 0; j < TY; ++j) nb[j] = sB[sn][ty + BY * j];
+                        for (int j = 0; j < TY; ++j) nb[j] = sB[sn][ty + by * j];
 #pragma unroll
                         for (int i = 0; i < TX; ++i)
 #pragma unroll
@@ -198,8 +203,8 @@ __attribute__((amdgpu_waves_per_eu(BTAB == 2 ? (TX * TY <= 9 ? 3 : 2) : 1))) voi
                     if (BTAB == 2) {
 #pragma unroll
                         for (int i = 0; i < TX; ++i) {
-                            a[i] = sA[2 * s][tx + BX * i];
-                            ai[i] = sA[2 * s + 1][tx + BX * i];
+                            a[i] = sA[2 * s][tx + bx * i];
+                            ai[i] = sA[2 * s + 1][tx + bx * i];
                         }
                     } else {
                         const Coef c = sC[t0 + s];
@@ -213,7 +218,7 @@ __attribute__((amdgpu_waves_per_eu(BTAB == 2 ? (TX * TY <= 9 ? 3 : 2) : 1))) voi
                     }
                     if (BTAB) {
 #pragma unroll
-                        for (int j = 0; j < TY; ++j) b[j] = sB[s][ty + BY * j];
+                        for (int j = 0; j < TY; ++j) b[j] = sB[s][ty + by * j];
                     } else {
                         const Coef c = sC[t0 + s];
 #pragma unroll
@@ -272,7 +277,7 @@ __attribute__((amdgpu_waves_per_eu(BTAB == 2 ? (TX * TY <= 9 ? 3 : 2) : 1))) voi
         // bound the reverse), so M u is split by sign into min(M u, 0) and
         // max(M u, 0), which feed separate sums without selects.
         double cx = lox, cy = loy, dx = hx, dy = hy;
-        int otx = tx, oty = ty;
+        int otx = idle ? p.nx : tx, oty = idle ? p.ny : ty;
         asm volatile("" : "+v"(cx), "+v"(cy), "+v"(dx), "+v"(dy), "+v"(otx), "+v"(oty));
         // The weights and moment polynomials are separable, M = wx wy,
         // |u|^2 / 2 = vx^2 / 2 + vy^2 / 2 and the sign of M u_k depends on
@@ -288,7 +293,7 @@ __attribute__((amdgpu_waves_per_eu(BTAB == 2 ? (TX * TY <= 9 ? 3 : 2) : 1))) voi
         for (int j = 0; j < TY; ++j) { ctn[j] = 0.0; ctx[j] = 0.0; }
 #pragma unroll
         for (int i = 0; i < TX; ++i) {
-            const int jx = otx + BX * i;
+            const int jx = otx + bx * i;
             if (jx >= p.nx) continue;
             const double vx = node_pos(cx, jx, dx);
             const double wx = dx * ((jx == 0 || jx == p.nx - 1) ? 0.5 : 1.0);
@@ -316,7 +321,7 @@ __attribute__((amdgpu_waves_per_eu(BTAB == 2 ? (TX * TY <= 9 ? 3 : 2) : 1))) voi
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
-                        const int jy = oty + BY * (j + h);
+                        const int jy = oty + by * (j + h);
                         // nodes past the grid (finite values) add zero
                         const double wy = jy < p.ny ? dy * ((jy == 0 || jy == p.ny - 1) ? 0.5 : 1.0) : 0.0;
                         const double gtn = exp_fin(pr[4 * h + 0], T[4 * h + 0]);
@@ -335,7 +340,7 @@ __attribute__((amdgpu_waves_per_eu(BTAB == 2 ? (TX * TY <= 9 ? 3 : 2) : 1))) voi
             } else {
 #pragma unroll
             for (int j = 0; j < TY; ++j) {
-                const int jy = oty + BY * j;
+                const int jy = oty + by * j;
                 if (jy >= p.ny) continue;
                 const double wy = dy * ((jy == 0 || jy == p.ny - 1) ? 0.5 : 1.0);
                 const double gtn = exp_tab(qtn[i][j], sExp);
@@ -368,7 +373,7 @@ __attribute__((amdgpu_waves_per_eu(BTAB == 2 ? (TX * TY <= 9 ? 3 : 2) : 1))) voi
         }
 #pragma unroll
         for (int j = 0; j < TY; ++j) {
-            const int jy = oty + BY * j;
+            const int jy = oty + by * j;
             if (jy >= p.ny) continue;
             const double vy = node_pos(cy, jy, dy);
             const double wy = dy * ((jy == 0 || jy == p.ny - 1) ? 0.5 : 1.0);

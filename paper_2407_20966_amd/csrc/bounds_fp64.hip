@@ -52,6 +52,13 @@ hipError_t launch_2d<16, 16, 2, 2, 0>(const BoundsArgs& a, hipStream_t stream) {
     return launch_bounds_fp64_small(a, 2, stream);
 }
 
+// the 48 x 48 table tile, on grids that leave a third of it unused split to fit
+template <>
+hipError_t launch_2d<16, 16, 3, 3, 2>(const BoundsArgs& a, hipStream_t stream) {
+    if (bounds_fp64_fit(a.nx, a.ny)) return launch_bounds_fp64_fit(a, stream);
+    return launch(bounds_fp64_2d<16, 16, 3, 3, 2>, kThreads, a, stream);
+}
+
 // mode 3: the kernel that culls states block by block
 template <>
 hipError_t launch_2d<16, 16, 4, 4, 3>(const BoundsArgs& a, hipStream_t stream) {

@@ -101,6 +101,9 @@ hipError_t launch_bounds_fp64(const BoundsArgs& a, int dim, hipStream_t stream, 
 hipError_t launch_bounds_fp64_1d(const BoundsArgs& a, hipStream_t stream);
 // The 16 x 16-thread tiles of one or 2 x 2 nodes per thread (nodes_per_thread 1, 2).
 hipError_t launch_bounds_fp64_small(const BoundsArgs& a, int nodes_per_thread, hipStream_t stream);
+// Grids within 48 x 48 that 256 threads cover with 2 x 3 nodes each.
+bool bounds_fp64_fit(int nx, int ny);
+hipError_t launch_bounds_fp64_fit(const BoundsArgs& a, hipStream_t stream);
 // Energy bounds from the per-state integrand (KBL_FLAG_ENERGY_PERSTATE).
 hipError_t launch_bounds_fp64_energy(const BoundsArgs& a, int dim, hipStream_t stream);
 // d = 3: FP64 bounds over a 3D velocity grid (tile < 0: default for the grid).
