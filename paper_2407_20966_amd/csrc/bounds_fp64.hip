@@ -100,16 +100,29 @@ int default_tile_2d(int nx, int ny) {
 // Whether the culling kernel (tile 14) is the default.  It walks one element
 // per wave, so it needs a few thousand elements to fill the chip, and its
 // gain grows with the grid (blocks become small against the width of the
-// Maxwellians) and with the stencil.
+// Maxwellians) and with the stencil.  Times of the other default over those of
+// the culling kernel, quads of 20, 45 and 80 states:
+//  - grids beyond 48 nodes: 0.94-1.11 at 2025 elements, 1.12-1.26 at 3025;
+//  - beyond 32 nodes, at most eight passes, no fit to the grid (40 x 40):
+//    1.04-1.07 at 2500, 1.17 at 3600, 1.3-1.5 at 40000;
+//  - beyond 32 nodes with a fit (36 x 41) or more passes (48 x 48): 0.8-0.97 and
+//    0.94-1.02 with 20 states; with 45 and more 0.9-1.0 at 6400 elements,
+//    1.0-1.1 at 10000, 1.16-1.22 at 40000;
+//  - up to 32 nodes (32 x 30): 0.87-0.95 with 20 states, with 45 and more 1.0 at
+//    6400, 1.02-1.15 from 10000 on; up to 28 nodes 0.86-1.01 (triangles of 84
+//    states 1.04-1.2).
+// Node stencils (n_s = 1, of 48 states with the same values on both sides of a
+// face) have longer lists: 0.9-0.99 up to 16000, 0.95-1.05 beyond.
 bool cull_pays(const BoundsArgs& a) {
     if (!bounds_cull_fits(a)) return false;
     const int n = a.nx > a.ny ? a.nx : a.ny;
-    if (n <= 24 || a.n_elem < 6000) return false;
+    if (n <= 24 || a.n_elem < 3000) return false;
     if (n > 48) return true;
     const int hw = (a.nx + 15) / 16, hh = (a.ny + 15) / 16;
     const int blocks = ((a.nx + 2 * hw - 1) / (2 * hw)) * ((a.ny + 2 * hh - 1) / (2 * hh));
-    if (blocks <= 8 * (64 / (hw * hh))) return true;
-    return a.n_elem >= 16384 && a.nnz * a.n_s >= 64 * a.n_elem;
+    if (n > 32 && blocks <= 8 * (64 / (hw * hh)) && !bounds_fp64_fit(a.nx, a.ny)) return true;
+    if (n <= 28) return a.n_elem >= 32768 && a.nnz * a.n_s >= 64 * a.n_elem;
+    return a.n_s > 1 && a.nnz * a.n_s >= 40 * a.n_elem && a.n_elem >= 8192;
 }
 
 }  // namespace
