@@ -47,6 +47,10 @@
 // hoisted constants spilled) took forward and backward there from 2.88 to
 // 2.72 ms, 3600 quads on 64 x 64 nodes from 1.10 to 0.95, 10000 of 45 states on
 // 16 x 16 from 460 to 395 us.
+// Grids that need no more than 2 x 3 (within 48 x 48) or 3 x 4 nodes per thread
+// get the threads split to fit them: forward and backward of 3600 quads of 45
+// states take 365 us on 33 x 41 nodes against 403 with 3 x 3, 540 us on 50 x 50
+// against 690 with 4 x 4.
 // A gather kernel then sums, for each node, the slots of listed elements that
 // refer to it, walking the (symmetric) stencil in CSR order.
 #include <type_traits>
@@ -90,7 +94,9 @@ __device__ __forceinline__ int key_index(double k) { return __double2loint(k) & 
 // four nodes per thread, the larger tiles would spill in their loops.
 constexpr int bwd_waves(int nodes) { return nodes <= 4 ? 3 : 2; }
 
-template <int D, int BX, int BY, int TX, int TY, bool F32>
+// FIT: the threads are split to fit the grid, ceil(nx / TX) by ceil(ny / TY); the
+// threads left over hold no node of it.
+template <int D, int BX, int BY, int TX, int TY, bool F32, bool FIT>
 __global__ __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(bwd_waves(TX * TY)))) void bounds_bwd_fp64(BwdArgs a) {
     constexpr int NT = BX * BY;
     constexpr int NW = NT / 64;
@@ -109,7 +115,8 @@ __global__ __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(bwd_wav
     const BoundsArgs& p = a.f;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wid = tid >> 6;
-    const int tx = tid % BX, ty = tid / BX;
+    const int bx = FIT ? (p.nx + TX - 1) / TX : BX;
+    const int tx = tid % bx, ty = tid / bx;
     const double rm = 1.0 - p.r_fac, rp = 1.0 + p.r_fac;
     const int64_t nslot = p.nnz * p.n_s;
 
@@ -578,10 +585,10 @@ __global__ __launch_bounds__(256) void bwd_status(BoundsArgs p, const uint32_t* 
 
 // A grid of up to 4096 workgroups walks the active list (its length is on
 // the device): a few per CU at a time, each taking every 4096th entry.
-template <int D, int BX, int BY, int TX, int TY, bool F32 = false>
+template <int D, int BX, int BY, int TX, int TY, bool F32 = false, bool FIT = false>
 hipError_t launch_bwd(const BwdArgs& a, hipStream_t stream) {
     const int64_t g = a.f.n_elem < 4096 ? a.f.n_elem : 4096;
-    hipLaunchKernelGGL((bounds_bwd_fp64<D, BX, BY, TX, TY, F32>), dim3((unsigned)g),
+    hipLaunchKernelGGL((bounds_bwd_fp64<D, BX, BY, TX, TY, F32, FIT>), dim3((unsigned)g),
                        dim3(BX * BY), 0, stream, a);
     return hipGetLastError();
 }
@@ -604,7 +611,9 @@ hipError_t launch_bounds_bwd_fp64(const BoundsArgs& f, const uint32_t* fstatus, 
         const int n = f.nx > f.ny ? f.nx : f.ny;
         if (n <= 16) err = launch_bwd<2, 16, 16, 1, 1, true>(a, stream);
         else if (n <= 32) err = launch_bwd<2, 16, 16, 2, 2, true>(a, stream);
+        else if (n <= 48 && tile_fits_grid<2, 3>(f)) err = launch_bwd<2, 16, 16, 2, 3, true, true>(a, stream);
         else if (n <= 48) err = launch_bwd<2, 16, 16, 3, 3, true>(a, stream);
+        else if (n <= 64 && tile_fits_grid<3, 4>(f)) err = launch_bwd<2, 16, 16, 3, 4, true, true>(a, stream);
         else if (n <= 64) err = launch_bwd<2, 16, 16, 4, 4, true>(a, stream);
         else return hipErrorInvalidValue;
     } else if (mixed) {
@@ -613,7 +622,9 @@ hipError_t launch_bounds_bwd_fp64(const BoundsArgs& f, const uint32_t* fstatus, 
         const int n = f.nx > f.ny ? f.nx : f.ny;
         if (n <= 16) err = launch_bwd<2, 16, 16, 1, 1>(a, stream);
         else if (n <= 32) err = launch_bwd<2, 16, 16, 2, 2>(a, stream);
+        else if (n <= 48 && tile_fits_grid<2, 3>(f)) err = launch_bwd<2, 16, 16, 2, 3, false, true>(a, stream);
         else if (n <= 48) err = launch_bwd<2, 16, 16, 3, 3>(a, stream);
+        else if (n <= 64 && tile_fits_grid<3, 4>(f)) err = launch_bwd<2, 16, 16, 3, 4, false, true>(a, stream);
         else if (n <= 64) err = launch_bwd<2, 16, 16, 4, 4>(a, stream);
         else return hipErrorInvalidValue;
     } else {

@@ -16,6 +16,9 @@
 // other waves hide the table reads.  90000 quads of 80 states on a 48 x 48 grid:
 // 4.44 ms, 4.85 with two waves; 40000 on 64 x 64: 3.37 ms, on 30 x 28: 1.05
 // (3.42 and 1.08 before machine LICM was turned off here).
+// Grids that need no more than 2 x 3 (within 48 x 48) or 3 x 4 nodes per thread
+// get the threads split to fit them: 22500 quads of 45 states on 33 x 41 nodes
+// take 619 us against 731 on the 3 x 3 tile, on 50 x 50 1.01 ms against 1.19.
 // Visiting only the states that can be an extremum in a block of nodes, block
 // by block as in bounds_cull_2d, does not pay here: it halves the pair work
 // (36 of 80 states survive in 12 x 12 nodes), but the blocks near ties keep
@@ -26,12 +29,14 @@
 namespace kbl {
 namespace {
 
-template <int BX, int BY, int TX, int TY>
+// FIT > 0: the threads are split to fit the grid, ceil(nx / TX) by ceil(ny / TY),
+// with FIT x FIT tables; the threads left over repeat thread 0 with weight zero.
+template <int BX, int BY, int TX, int TY, int FIT = 0>
 __global__ __launch_bounds__(BX * BY)
-__attribute__((amdgpu_waves_per_eu(TX * TY == 16 ? 2 : TX * TY == 9 ? 3 : 4))) void bounds_fp64_2d_energy(BoundsArgs p) {
+__attribute__((amdgpu_waves_per_eu(TX * TY >= 12 ? 2 : TX * TY == 9 ? 3 : 4))) void bounds_fp64_2d_energy(BoundsArgs p) {
     constexpr int NT = BX * BY;
-    constexpr int NXM = BX * TX;
-    constexpr int NYM = BY * TY;
+    constexpr int NXM = FIT ? FIT : BX * TX;
+    constexpr int NYM = FIT ? FIT : BY * TY;
     constexpr int kTabStates = 32;
     static_assert(NT % 64 == 0 && NT <= kThreads, "workgroup must be 1-4 waves");
     __shared__ Coef sC[kMaxStates];
@@ -43,7 +48,10 @@ __attribute__((amdgpu_waves_per_eu(TX * TY == 16 ? 2 : TX * TY == 9 ? 3 : 4))) v
     static_assert(NXM == NYM && NXM <= NT, "tables built by columns");
 
     const int tid = threadIdx.x;
-    const int tx = tid % BX, ty = tid / BX;
+    const int bx = FIT ? (p.nx + TX - 1) / TX : BX;
+    const int by = FIT ? (p.ny + TY - 1) / TY : BY;
+    const bool idle = FIT && tid >= bx * by;
+    const int tx = idle ? 0 : tid % bx, ty = idle ? 0 : tid / bx;
     const double rm = 1.0 - p.r_fac, rp = 1.0 + p.r_fac;
     stage_exp_table<NT>(sExp);   // published by the prologue's barriers
 
@@ -67,13 +75,13 @@ __attribute__((amdgpu_waves_per_eu(TX * TY == 16 ? 2 : TX * TY == 9 ? 3 : 4))) v
         double ux[TX], uy[TY], hux[TX], huy[TY];
 #pragma unroll
         for (int i = 0; i < TX; ++i) {
-            const int j = tx + BX * i;
+            const int j = tx + bx * i;
             ux[i] = node_pos(lox, j < p.nx ? j : p.nx - 1, hx);
             hux[i] = 0.5 * ux[i] * ux[i];
         }
 #pragma unroll
         for (int j = 0; j < TY; ++j) {
-            const int jj = ty + BY * j;
+            const int jj = ty + by * j;
             uy[j] = node_pos(loy, jj < p.ny ? jj : p.ny - 1, hy);
             huy[j] = 0.5 * uy[j] * uy[j];
         }
@@ -117,11 +125,11 @@ __attribute__((amdgpu_waves_per_eu(TX * TY == 16 ? 2 : TX * TY == 9 ? 3 : 4))) v
                     double ea[TX], hc[TX], eb[TY];
 #pragma unroll
                     for (int i = 0; i < TX; ++i) {
-                        ea[i] = sEA[0][tx + BX * i];
+                        ea[i] = sEA[0][tx + bx * i];
                         hc[i] = hux[i] + cs;
                     }
 #pragma unroll
-                    for (int j = 0; j < TY; ++j) eb[j] = sEB[0][ty + BY * j];
+                    for (int j = 0; j < TY; ++j) eb[j] = sEB[0][ty + by * j];
 #pragma unroll
                     for (int i = 0; i < TX; ++i)
 #pragma unroll
@@ -141,11 +149,11 @@ __attribute__((amdgpu_waves_per_eu(TX * TY == 16 ? 2 : TX * TY == 9 ? 3 : 4))) v
                     double ea[TX], hc[TX], eb[TY];
 #pragma unroll
                     for (int i = 0; i < TX; ++i) {
-                        ea[i] = sEA[s][tx + BX * i];
+                        ea[i] = sEA[s][tx + bx * i];
                         hc[i] = hux[i] + cs;
                     }
 #pragma unroll
-                    for (int j = 0; j < TY; ++j) eb[j] = sEB[s][ty + BY * j];
+                    for (int j = 0; j < TY; ++j) eb[j] = sEB[s][ty + by * j];
 #pragma unroll
                     for (int i = 0; i < TX; ++i)
 #pragma unroll
@@ -171,13 +179,13 @@ __attribute__((amdgpu_waves_per_eu(TX * TY == 16 ? 2 : TX * TY == 9 ? 3 : 4))) v
         for (int j = 0; j < TY; ++j) { cn[j] = 0.0; cx[j] = 0.0; }
 #pragma unroll
         for (int i = 0; i < TX; ++i) {
-            const int jx = tx + BX * i;
-            if (jx >= p.nx) continue;
+            const int jx = tx + bx * i;
+            if (idle || jx >= p.nx) continue;
             const double wx = hx * ((jx == 0 || jx == p.nx - 1) ? 0.5 : 1.0);
             double rn = 0.0, rx = 0.0, ren = 0.0, rex = 0.0;   // per row: sum over y of wy g, wy e
 #pragma unroll
             for (int j = 0; j < TY; ++j) {
-                const int jy = ty + BY * j;
+                const int jy = ty + by * j;
                 if (jy >= p.ny) continue;
                 const double wy = hy * ((jy == 0 || jy == p.ny - 1) ? 0.5 : 1.0);
                 rn = fma(wy, gn[i][j], rn);
@@ -200,8 +208,8 @@ __attribute__((amdgpu_waves_per_eu(TX * TY == 16 ? 2 : TX * TY == 9 ? 3 : 4))) v
         }
 #pragma unroll
         for (int j = 0; j < TY; ++j) {
-            const int jy = ty + BY * j;
-            if (jy >= p.ny) continue;
+            const int jy = ty + by * j;
+            if (idle || jy >= p.ny) continue;
             const double wy = hy * ((jy == 0 || jy == p.ny - 1) ? 0.5 : 1.0);
             const double mu = wy * uy[j];
             const double neg = fmin(mu, 0.0), pos = fmax(mu, 0.0);
@@ -302,7 +310,11 @@ hipError_t launch_bounds_fp64_energy(const BoundsArgs& a, int dim, hipStream_t s
         const int n = a.nx > a.ny ? a.nx : a.ny;
         if (n <= 16) return launch(bounds_fp64_2d_energy<16, 16, 1, 1>, 256, a, stream);
         if (n <= 32) return launch(bounds_fp64_2d_energy<16, 16, 2, 2>, 256, a, stream);
+        if (n <= 48 && tile_fits_grid<2, 3>(a))
+            return launch(bounds_fp64_2d_energy<16, 16, 2, 3, 48>, 256, a, stream);
         if (n <= 48) return launch(bounds_fp64_2d_energy<16, 16, 3, 3>, 256, a, stream);
+        if (n <= 64 && tile_fits_grid<3, 4>(a))
+            return launch(bounds_fp64_2d_energy<16, 16, 3, 4, 64>, 256, a, stream);
         if (n <= 64) return launch(bounds_fp64_2d_energy<16, 16, 4, 4>, 256, a, stream);
         return hipErrorInvalidValue;
     }

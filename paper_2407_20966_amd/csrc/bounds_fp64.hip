@@ -52,11 +52,17 @@ hipError_t launch_2d<16, 16, 2, 2, 0>(const BoundsArgs& a, hipStream_t stream) {
     return launch_bounds_fp64_small(a, 2, stream);
 }
 
-// the 48 x 48 table tile, on grids that leave a third of it unused split to fit
+// the table tiles, split to fit grids that leave a third or a quarter of them
+// unused (a grid within 48 x 48 keeps the 64 x 64 tile if that was asked for)
 template <>
 hipError_t launch_2d<16, 16, 3, 3, 2>(const BoundsArgs& a, hipStream_t stream) {
-    if (bounds_fp64_fit(a.nx, a.ny)) return launch_bounds_fp64_fit(a, stream);
+    if (bounds_fp64_fit(a)) return launch_bounds_fp64_fit(a, stream);
     return launch(bounds_fp64_2d<16, 16, 3, 3, 2>, kThreads, a, stream);
+}
+template <>
+hipError_t launch_2d<16, 16, 4, 4, 2>(const BoundsArgs& a, hipStream_t stream) {
+    if ((a.nx > 48 || a.ny > 48) && bounds_fp64_fit(a)) return launch_bounds_fp64_fit(a, stream);
+    return launch(bounds_fp64_2d<16, 16, 4, 4, 2>, kThreads, a, stream);
 }
 
 // mode 3: the kernel that culls states block by block
@@ -120,7 +126,7 @@ bool cull_pays(const BoundsArgs& a) {
     if (n > 48) return true;
     const int hw = (a.nx + 15) / 16, hh = (a.ny + 15) / 16;
     const int blocks = ((a.nx + 2 * hw - 1) / (2 * hw)) * ((a.ny + 2 * hh - 1) / (2 * hh));
-    if (n > 32 && blocks <= 8 * (64 / (hw * hh)) && !bounds_fp64_fit(a.nx, a.ny)) return true;
+    if (n > 32 && blocks <= 8 * (64 / (hw * hh)) && !bounds_fp64_fit(a)) return true;
     if (n <= 28) return a.n_elem >= 32768 && a.nnz * a.n_s >= 64 * a.n_elem;
     return a.n_s > 1 && a.nnz * a.n_s >= 40 * a.n_elem && a.n_elem >= 8192;
 }

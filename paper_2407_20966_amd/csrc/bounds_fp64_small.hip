@@ -1,6 +1,6 @@
 // The 2D FP64 bounds kernel on grids of up to 16 x 16 and 32 x 32 nodes and on
-// those within 48 x 48 that need no more than 2 x 3 nodes per thread, compiled
-// without machine LICM, gfx950.
+// larger ones that need no more than 2 x 3 (within 48 x 48) or 3 x 4 nodes per
+// thread, compiled without machine LICM, gfx950.
 //
 // What bounds it: VALU issue, with the prologue's logs and the contraction's
 // exps a large part beside one or four nodes per thread.  Machine LICM hoists
@@ -24,14 +24,18 @@ hipError_t launch_bounds_fp64_small(const BoundsArgs& a, int nodes_per_thread, h
 // nodes instead of nine, in 119 VGPRs and 33 KB of LDS (tables of 16 states):
 // four workgroups per CU instead of three.  2025 quads of 45 states: 57 against
 // 75 us on 33 x 41 nodes, 55 against 71 on 36 x 36; 400 on 44 x 25: 25.6
-// against 30.
-bool bounds_fp64_fit(int nx, int ny) {
-    return nx <= 48 && ny <= 48 && ((nx + 1) / 2) * ((ny + 2) / 3) <= kThreads;
+// against 30.  Likewise beyond 48 nodes with 3 x 4 nodes per thread instead of
+// 4 x 4: 2025 quads of 45 states on 50 x 50 102 us against 112.
+bool bounds_fp64_fit(const BoundsArgs& a) {
+    return a.nx <= 48 && a.ny <= 48 ? tile_fits_grid<2, 3>(a)
+                                    : a.nx <= 64 && a.ny <= 64 && tile_fits_grid<3, 4>(a);
 }
 
 hipError_t launch_bounds_fp64_fit(const BoundsArgs& a, hipStream_t stream) {
-    if (!bounds_fp64_fit(a.nx, a.ny)) return hipErrorInvalidValue;
-    return launch(bounds_fp64_2d<16, 16, 2, 3, 2, 48>, kThreads, a, stream);
+    if (!bounds_fp64_fit(a)) return hipErrorInvalidValue;
+    if (a.nx <= 48 && a.ny <= 48)
+        return launch(bounds_fp64_2d<16, 16, 2, 3, 2, 48>, kThreads, a, stream);
+    return launch(bounds_fp64_2d<16, 16, 3, 4, 2, 64>, kThreads, a, stream);
 }
 
 }  // namespace kbl

@@ -101,8 +101,14 @@ hipError_t launch_bounds_fp64(const BoundsArgs& a, int dim, hipStream_t stream, 
 hipError_t launch_bounds_fp64_1d(const BoundsArgs& a, hipStream_t stream);
 // The 16 x 16-thread tiles of one or 2 x 2 nodes per thread (nodes_per_thread 1, 2).
 hipError_t launch_bounds_fp64_small(const BoundsArgs& a, int nodes_per_thread, hipStream_t stream);
-// Grids within 48 x 48 that 256 threads cover with 2 x 3 nodes each.
-bool bounds_fp64_fit(int nx, int ny);
+// Whether 256 threads with TX x TY nodes each cover the grid.
+template <int TX, int TY>
+inline bool tile_fits_grid(const BoundsArgs& a) {
+    return ((a.nx + TX - 1) / TX) * ((a.ny + TY - 1) / TY) <= 256;
+}
+// Grids within 48 x 48 that 256 threads cover with 2 x 3 nodes each, larger ones
+// that they cover with 3 x 4.
+bool bounds_fp64_fit(const BoundsArgs& a);
 hipError_t launch_bounds_fp64_fit(const BoundsArgs& a, hipStream_t stream);
 // Energy bounds from the per-state integrand (KBL_FLAG_ENERGY_PERSTATE).
 hipError_t launch_bounds_fp64_energy(const BoundsArgs& a, int dim, hipStream_t stream);
