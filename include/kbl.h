@@ -173,12 +173,12 @@ kbl_status kbl_compute_bounds_nodes(const kbl_params* params, int32_t dim, int64
  *   KBL_PERSISTENT_BLOCKS=<g>  grid of g workgroups walking the elements
  *                              (0 = one workgroup per element, -k = k
  *                              elements per workgroup)
- * Without either, a 2D launch has each workgroup compute two elements (half
- * as many workgroups as elements), a 1D or 3D launch one workgroup per
- * element.  The 2D FP64 tile 14 has one element per wave, four waves per
- * workgroup: there a choice of k elements per workgroup means k per wave, and
- * large 2D launches use it with two elements per wave (one below 65536
- * elements).
+ * Without either, a 2D launch from 8192 elements on has each workgroup compute
+ * two elements (half as many workgroups as elements), a smaller one and a 1D
+ * or 3D launch one workgroup per element.  The 2D FP64 tile 14 has one element
+ * per wave, four waves per workgroup: there a choice of k elements per
+ * workgroup means k per wave, and large 2D launches use it with two elements
+ * per wave (one below 65536 elements).
  */
 /*
  * kbl_autotune_bounds - picks the launch configuration of kbl_compute_bounds

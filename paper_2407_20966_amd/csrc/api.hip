@@ -17,6 +17,8 @@ constexpr int kMax2DNodesPerDim = 64;
 constexpr int kMax3DNodesPerDim = 64;
 constexpr int kMax1DNodes = 4096;
 constexpr int kMax1DBackwardNodes = 2048;
+// 2D meshes from this size on are launched with two elements per workgroup.
+constexpr int64_t kTwoPerWorkgroup = 8192;
 
 // delta = 2/(gamma-1) - d (Sec. 3.6); tiny negative round-off is clamped to 0.
 bool internal_dof(int dim, double gamma, double* half_delta) {
@@ -76,8 +78,13 @@ kbl_status make_bounds_args(const kbl_params* params, int32_t dim, int64_t n_ele
     // default launch: two elements per workgroup in 2D (the workgroup's
     // set-up, the exp table's staging among it, serves two elements: 1-5%
     // faster than one per element over the FP64, mixed and per-state
-    // energy tiles), one workgroup per element otherwise
-    a->grid_blocks = dim == 2 ? -2 : 0;
+    // energy tiles), one workgroup per element otherwise.  Meshes of a few
+    // workgroups per CU get one element per workgroup too: two leave CUs idle
+    // below a thousand elements and a longer last round up to some thousands
+    // (48 x 48 nodes, FP64: 144 elements 31 -> 17 us, 400 32 -> 23, 2025 73 -> 66,
+    // 5625 173 -> 173, 10000 191 -> 193; FP32 400 35 -> 21, 2500 80 -> 70, 6400 167 ->
+    // 162, though 2025, where two fill the chip exactly once, 56 -> 60).
+    a->grid_blocks = dim == 2 && n_elem >= kTwoPerWorkgroup ? -2 : 0;
     a->nx = g.n[0];
     a->ny = dim >= 2 ? g.n[1] : 1;
     a->nz = dim == 3 ? g.n[2] : 1;
