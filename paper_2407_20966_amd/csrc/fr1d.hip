@@ -23,7 +23,6 @@
 #include <math.h>
 #include <string.h>
 
-
 #include "fr1d_internal.h"
 
 namespace kbl {
