@@ -2,6 +2,8 @@
 // moments, shared by the 1D bounds kernel and the fused stage of the 1D solver.
 #pragma once
 
+#include <type_traits>
+
 #include "bounds_common.h"
 
 namespace kbl {
@@ -42,6 +44,67 @@ struct Sums1D {
         part[6] = part[7] = 0.0;
     }
 };
+
+// Which of S <= 64 staged states can hold an extremum of g or g_I at the wave's
+// nodes of a round: the wave owns 64 T consecutive nodes of a round of NT T.
+// With c the middle of those nodes, w their half width and r the state whose q
+// is largest at c,
+//   q_i - q_r <= (q_i - q_r)(c) + w |dg| + w^2 max(nk_i - nk_r, 0),
+// and a state for which that plus max(l_i - l_r, 0) is negative is neither
+// maximum; likewise from below.  Half widths and thresholds are widened by
+// 1e-10, far above rounding, so the envelopes are those of all states.
+// 64 / 2^lg rounds from `round` on at once: lane = (round, state mod 2^lg).
+// Returns their masks side by side; the mask of a round past the grid is 0.
+template <int NT, int T>
+__device__ __forceinline__ unsigned long long cull_1d(const BoundsArgs& p, const Coef* sC, int S,
+                                                      double lo, double h, int round, int lg) {
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int s = lane & ((1 << lg) - 1);
+    const int ja = (round + (lane >> lg)) * NT * T + wid * 64 * T;
+    const int jb = min(ja + 64 * T, p.nx) - 1;
+    const double x0 = node_pos(lo, ja, h), x1 = node_pos(lo, jb, h);
+    const double cx = 0.5 * (x0 + x1);
+    // twice the half width (the gradients below are halved), widened
+    const double w = fabs(x1 - x0) * (1.0 + 1e-10) + 1e-14 * (fabs(x0) + fabs(x1));
+    const double Q = 0.25 * w * w;
+    const bool internal = p.half_delta > 0.0, live = s < S;
+    const Coef c = sC[live ? s : 0];
+    const double d = cx - c.ux, t = c.nk * d, v = fma(t, d, c.a), qn = Q * c.nk;
+    const double l = internal ? c.al - c.a : 0.0;
+    // the state's index in the low bits: the reference found is the extremum
+    // up to 2^-17 relative, and any state is a valid reference
+    const float key = __int_as_float((__float_as_int((float)v) & ~63) | s);
+    float kmax = live ? key : -kInfF, kmin = live ? key : kInfF;
+    auto dpp = [](float x, auto ctrl) {
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x),
+                                                          decltype(ctrl)::value, 0xF, 0xF, false));
+    };
+    auto step = [&](auto ctrl) {
+        kmax = fmaxf(kmax, dpp(kmax, ctrl));
+        kmin = fminf(kmin, dpp(kmin, ctrl));
+    };
+    step(std::integral_constant<int, kDppXor1>{});
+    step(std::integral_constant<int, kDppXor2>{});
+    step(std::integral_constant<int, kDppHalfMirror>{});
+    step(std::integral_constant<int, kDppMirror>{});
+    for (int o = 16; o < (1 << lg); o <<= 1) {
+        kmax = fmaxf(kmax, __shfl_xor(kmax, o, 64));
+        kmin = fminf(kmin, __shfl_xor(kmin, o, 64));
+    }
+    bool keep = false;
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+        const Coef r = sC[__float_as_int(side ? kmin : kmax) & 63];
+        const double dr = cx - r.ux, tr = r.nk * dr, vr = fma(tr, dr, r.a), qr = Q * r.nk;
+        const double lr = internal ? r.al - r.a : 0.0;
+        const double slack = 1e-10 * (1.0 + fabs(vr) + fabs(r.a) + w * fabs(tr) + fabs(qr) + fabs(lr));
+        const double sg = side ? -1.0 : 1.0;
+        const double b = fma(w, fabs(t - tr), sg * (v - vr)) + fmax(sg * (l - lr), 0.0) +
+                         fmax(sg * (qn - qr), 0.0);
+        keep = keep || b >= -slack;
+    }
+    return __builtin_amdgcn_ballot_w64(keep && live && ja < p.nx);
+}
 
 // Envelopes of T nodes of a 1D velocity grid (node j0 + stride i) and their
 // moments.  No separability to exploit: a pair costs sub, mul and two fma
@@ -84,6 +147,47 @@ struct Env1D {
                 qin[i] = raw_min(qin[i], qi);
                 qix[i] = raw_max(qix[i], qi);
             }
+        }
+    }
+    // The states of a mask (not 0, the same in every lane); the next state's
+    // coefficients are read before the current state's work.
+    __device__ __forceinline__ void fold_mask(const BoundsArgs& p, const Coef* sC,
+                                              unsigned long long m, double lo, double h, int j0,
+                                              int stride) {
+        double u[T];
+#pragma unroll
+        for (int i = 0; i < T; ++i) u[i] = node(p, lo, h, j0 + stride * i);
+        auto next = [&]() {
+            const int s = __builtin_ctzll(m);
+            m &= m - 1;
+            return sC[s];
+        };
+        Coef c = next();
+#pragma unroll
+        for (int i = 0; i < T; ++i) {
+            const double d = u[i] - c.ux;
+            const double t = c.nk * d;
+            qtn[i] = qtx[i] = fma(t, d, c.a);
+            qin[i] = qix[i] = fma(t, d, c.al);
+        }
+        if (m == 0) return;
+        Coef n = next();
+        for (;;) {
+            c = n;
+            const bool last = m == 0;
+            if (!last) n = next();
+#pragma unroll
+            for (int i = 0; i < T; ++i) {
+                const double d = u[i] - c.ux;
+                const double t = c.nk * d;
+                const double q = fma(t, d, c.a);
+                const double qi = fma(t, d, c.al);
+                qtn[i] = raw_min(qtn[i], q);
+                qtx[i] = raw_max(qtx[i], q);
+                qin[i] = raw_min(qin[i], qi);
+                qix[i] = raw_max(qix[i], qi);
+            }
+            if (last) break;
         }
     }
     // Adds the nodes' moments to the unrelaxed envelope sums (the momentum

@@ -7,15 +7,22 @@ namespace kbl {
 namespace {
 
 // One workgroup per element; the nodes go in rounds of NT T (thread t owns
-// nodes t + NT i of a round).
+// nodes t + NT i of a round, with CULL a wave 64 T consecutive ones).
 // What bounds it: VALU issue, 8 ops per (state, node) and 77 per node for the
 // four exps and the moments.  Two nodes per thread and round and at most 96
 // VGPRs keep five waves on a SIMD to cover the prologue, the exp table reads
-// and the barriers: 20000 stencils of 12 states take 249 us with 2048 nodes,
-// 140 with 1000 and 108 with 500 (290, 171 and 118 with all of a thread's
-// nodes at once, in up to 168 VGPRs; four nodes per round, four waves: 254,
-// 145, 159); 30000 with 200 nodes take 125 us against 144.
-template <int NT, int T>
+// and the barriers: 20000 stencils of 12 states take 253 us with 2048 nodes,
+// 9 states 140 with 1000, 12 states 108 with 500 (290, 171 and 118 with all of
+// a thread's nodes at once, in up to 168 VGPRs; four nodes per round, four
+// waves: 254, 145, 159); 30000 with 200 nodes take 124 us against 144.
+// CULL (grids beyond 512 nodes, ten states and more): a wave's 128 nodes of a
+// round are a block over which five of 12 or seven of 18 states can be an
+// extremum.  Lane = (round, state) bounds up to four rounds at once, the ballot is
+// the mask of states to visit.  2048 nodes: 12 states 203 us against 253, 18
+// states 231 against 315; 700 nodes, 12 states 132 against 153; where states
+// tie all are visited in the plain loop (308 against 313 with a constant field).
+// The 1D solver's stencils of 6 to 12 states gain nothing by it.
+template <int NT, int T, bool CULL>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(5)))
 void bounds_fp64_1d(BoundsArgs p) {
     __shared__ Coef sC[kMaxStates];
@@ -42,10 +49,31 @@ void bounds_fp64_1d(BoundsArgs p) {
         const double h = (box[1] - box[0]) / (double)(p.nx - 1);
         Sums1D sum1;
         if (S <= kMaxStates) {
-            for (int j0 = 0; j0 < p.nx; j0 += NT * T) {
-                Env1D<T> env;
-                env.fold(p, sC, (int)S, lo, h, j0 + tid, NT, true);
-                env.contract(p, lo, h, j0 + tid, NT, sExp, sum1);
+            const int rounds = (p.nx + NT * T - 1) / (NT * T);
+            if (CULL && S >= 10 && S <= 64 && S * rounds >= 24) {
+                // the waves take consecutive runs of nodes and visit the
+                // states that can be an extremum there
+                const int lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+                const int lg = S <= 16 ? 4 : S <= 32 ? 5 : 6;
+                unsigned long long bits = 0;
+                for (int r = 0; r < rounds; ++r) {
+                    const int sub = r & ((64 >> lg) - 1);
+                    if (sub == 0) bits = cull_1d<NT, T>(p, sC, (int)S, lo, h, r, lg);
+                    const unsigned long long m = (bits >> (sub << lg)) & (~0ull >> (64 - (1 << lg)));
+                    if (m == 0) break;         // past the grid
+                    const int j0 = r * NT * T + wid * 64 * T + lane;
+                    Env1D<T> env;
+                    // (nearly) tied states: all of them in the plain loop
+                    if (8 * __popcll(m) > 7 * (int)S) env.fold(p, sC, (int)S, lo, h, j0, 64, true);
+                    else env.fold_mask(p, sC, m, lo, h, j0, 64);
+                    env.contract(p, lo, h, j0, 64, sExp, sum1);
+                }
+            } else {
+                for (int j0 = 0; j0 < p.nx; j0 += NT * T) {
+                    Env1D<T> env;
+                    env.fold(p, sC, (int)S, lo, h, j0 + tid, NT, true);
+                    env.contract(p, lo, h, j0 + tid, NT, sExp, sum1);
+                }
             }
         } else {
             // chunks of states, staged again in every round; one node per
@@ -68,9 +96,9 @@ void bounds_fp64_1d(BoundsArgs p) {
     }
 }
 
-template <int NT, int T>
+template <int NT, int T, bool CULL = false>
 hipError_t launch_1d(const BoundsArgs& a, hipStream_t stream) {
-    hipLaunchKernelGGL((bounds_fp64_1d<NT, T>), dim3(bounds_grid(a)), dim3(NT), 0, stream, a);
+    hipLaunchKernelGGL((bounds_fp64_1d<NT, T, CULL>), dim3(bounds_grid(a)), dim3(NT), 0, stream, a);
     return hipGetLastError();
 }
 
@@ -79,6 +107,10 @@ hipError_t launch_1d(const BoundsArgs& a, hipStream_t stream) {
 hipError_t launch_bounds_fp64_1d(const BoundsArgs& a, hipStream_t stream) {
     if (a.nx <= 64) return launch_1d<64, 1>(a, stream);
     if (a.nx <= 256) return launch_1d<256, 1>(a, stream);
+    // a pass of the cull costs a wave about 80 ops, a state left out 16 per
+    // round of 512 nodes: from two rounds and a dozen states on (below that the
+    // plain kernel is 3-5% faster)
+    if (a.nx > 512 && a.nnz * a.n_s >= 10 * a.n_elem) return launch_1d<256, 2, true>(a, stream);
     return launch_1d<256, 2>(a, stream);
 }
 

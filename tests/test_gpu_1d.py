@@ -131,3 +131,39 @@ def test_bounds_1d(kbl, n_s, width, nu):
     err = (np.abs(b - rb) / np.maximum(a, 1e-300)).max()   # a bound may underflow to 0
     print(f"[1d] err {err:.2e}", flush=True)
     assert err <= 1e-12
+
+
+# state counts around the cull's lane groups (16, 32, 64) and its lower bound (10),
+# grids of two to nine rounds with a remainder; wide boxes, no internal degrees of
+# freedom, and states that tie (all equal, nearly equal)
+@pytest.mark.parametrize("n_s,width,nu", [(5, 2, 4096), (3, 4, 513), (4, 4, 2048), (17, 1, 700),
+                                          (16, 2, 1025), (11, 3, 1500), (16, 4, 2048),
+                                          (13, 5, 1100), (3, 3, 2048)])
+@pytest.mark.parametrize("kind", ["wide", "monatomic", "equal", "near"])
+def test_bounds_1d_cull(kbl, n_s, width, nu, kind):
+    rng = np.random.default_rng(7 * n_s + nu)
+    n, gamma = 24, 3.0 if kind == "monatomic" else 1.4
+    U = states_1d(rng, (n, n_s), gamma, 0.2)
+    if kind in ("equal", "near"):
+        U = np.broadcast_to(U[:, :1, :1], U.shape) * (
+            1.0 + (1e-9 if kind == "near" else 0.0) * rng.uniform(-1, 1, U.shape))
+    U = np.ascontiguousarray(U.reshape(3, -1))
+    cols = ((np.arange(n)[:, None] + np.arange(width)[None]) % n).astype(np.int32).reshape(-1)
+    rowptr = np.arange(0, n * width + 1, width, dtype=np.int32)
+    box = dict(lo=(-40.0,), hi=(35.0,)) if kind == "wide" else dict(k=8.0)
+    mode = kbl.GRID_GLOBAL if kind == "wide" else kbl.GRID_STENCIL
+    dev = torch.device("cuda:0")
+    t = lambda a: torch.from_numpy(a).to(dev)
+    print(f"[1d] cull {kind} states {n_s * width} nodes {nu}", flush=True)
+    b, s = kbl.compute_bounds(t(U), t(rowptr), t(cols), n_s, kbl.make_vgrid(mode, (nu,), **box),
+                              kbl.make_params(gamma))
+    rb, rs = oracle.bounds(1, gamma, U, rowptr, cols, n_s, mode, (nu,), r_fac=1e-3,
+                           **{**box, "lo": (*box.get("lo", (0.0,)), 0.0),
+                              "hi": (*box.get("hi", (0.0,)), 0.0)})
+    b = b.cpu().numpy()
+    assert np.array_equal(s.cpu().numpy().view(np.uint32), rs)
+    a = np.abs(rb)
+    a[[1, 4]] = np.maximum(a[[1, 4]], np.sqrt(a[3] * a[5]))
+    err = (np.abs(b - rb) / np.maximum(a, 1e-300)).max()
+    print(f"[1d] err {err:.2e}", flush=True)
+    assert err <= 1e-12
