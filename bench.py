@@ -66,7 +66,8 @@ WORKLOAD_TEXT = {
 
 # sources of the FP64 bounds kernels, per velocity dimension
 KERNEL_SOURCES = {
-    2: ("paper_2407_20966_amd/csrc/bounds_fp64.hip",
+    2: ("paper_2407_20966_amd/csrc/bounds_fp64.hip", "paper_2407_20966_amd/csrc/bounds_2d.h",
+        "paper_2407_20966_amd/csrc/bounds_fp64_small.hip",
         "paper_2407_20966_amd/csrc/bounds_cull_2d.hip",
         "paper_2407_20966_amd/csrc/bounds_common.h",
         "paper_2407_20966_amd/csrc/kbl_internal.h", "paper_2407_20966_amd/csrc/exp2_table.h"),

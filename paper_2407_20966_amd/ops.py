@@ -89,7 +89,7 @@ def _out(t: Optional[torch.Tensor], name: str, dtype: torch.dtype, device, shape
     shape (the kernels write every entry of it), or a new one (like: a tensor
     of this dtype and device)."""
     if t is None:
-        if like is not None:
+        if type(like) is torch.Tensor:      # a subclass would make outputs of its own
             return like.new_empty(shape)
         return torch.empty(shape, dtype=dtype, device=device)
     _check(t, name, dtype, device)
