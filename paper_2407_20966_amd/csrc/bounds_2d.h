@@ -16,7 +16,7 @@ namespace {
 // over repeat thread 0 with weight zero.
 template <int BX, int BY, int TX, int TY, int BTAB, int FIT = 0>
 __global__ __launch_bounds__(BX * BY)
-__attribute__((amdgpu_waves_per_eu(FIT ? (TX * TY <= 6 ? 4 : 2) : BTAB == 2 ? (TX * TY <= 9 ? 3 : 2) : 1))) void bounds_fp64_2d(BoundsArgs p) {
+__attribute__((amdgpu_waves_per_eu(FIT ? (TX * TY <= 3 ? 5 : TX * TY <= 6 ? 4 : 2) : BTAB == 2 ? (TX * TY <= 9 ? 3 : 2) : 1))) void bounds_fp64_2d(BoundsArgs p) {
     constexpr int NT = BX * BY;
     constexpr int NXM = FIT ? FIT : BX * TX;
     constexpr int NYM = FIT ? FIT : BY * TY;

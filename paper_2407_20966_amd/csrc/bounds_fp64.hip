@@ -116,7 +116,8 @@ int default_tile_2d(int nx, int ny) {
 //    1.0-1.1 at 10000, 1.16-1.22 at 40000;
 //  - up to 32 nodes (32 x 30): 0.87-0.95 with 20 states, with 45 and more 1.0 at
 //    6400, 1.02-1.15 from 10000 on; up to 28 nodes 0.86-1.01 (triangles of 84
-//    states 1.04-1.2).
+//    states 1.04-1.2); below 0.9 on those that one to three nodes per thread
+//    cover (30 x 16).
 // Node stencils (n_s = 1, of 48 states with the same values on both sides of a
 // face) have longer lists: 0.9-0.99 up to 16000, 0.95-1.05 beyond.
 bool cull_pays(const BoundsArgs& a) {
@@ -124,6 +125,7 @@ bool cull_pays(const BoundsArgs& a) {
     const int n = a.nx > a.ny ? a.nx : a.ny;
     if (n <= 24 || a.n_elem < 3000) return false;
     if (n > 48) return true;
+    if (n <= 32 && tile_fits_grid<1, 3>(a)) return false;
     const int hw = (a.nx + 15) / 16, hh = (a.ny + 15) / 16;
     const int blocks = ((a.nx + 2 * hw - 1) / (2 * hw)) * ((a.ny + 2 * hh - 1) / (2 * hh));
     if (n > 32 && blocks <= 8 * (64 / (hw * hh)) && !bounds_fp64_fit(a)) return true;

@@ -1,6 +1,6 @@
 """Kernels whose threads are split to fit the velocity grid, at the edges of the
-split: the table tiles (11 and 12) against the oracle and the tiles without
-tables, with stencils beyond one chunk of tables and of states; the per-state
+split: tile 1 and the table tiles (11 and 12) against the oracle and the tiles
+that are not split, with stencils beyond one chunk of tables and of states; the per-state
 energy bounds and the backward against the oracle."""
 
 import numpy as np
@@ -19,11 +19,13 @@ pytestmark = pytest.mark.gpu
 TOL = 1e-12          # the FP64 paths' bar against the oracle
 
 
-# one thread, one row or column of threads, all 256 threads (32 x 48, 48 x 30
-# nodes), remainders in both directions; (48, 33), (64, 47) and (49, 64) do not fit
+# one thread, one row or column of threads, all 256 threads (32 x 16, 16 x 32, 32 x
+# 48, 48 x 30 nodes), remainders in both directions; (29, 28), (48, 33), (64, 47) and
+# (49, 64) do not fit
 @pytest.mark.parametrize("n", [(2, 2), (2, 48), (48, 2), (3, 4), (32, 48), (31, 46), (48, 30),
                                (47, 29), (33, 41), (41, 35), (48, 33), (50, 50), (49, 60), (60, 49), (64, 44),
-                               (3, 64), (49, 2), (64, 47), (49, 64)])
+                               (3, 64), (49, 2), (64, 47), (49, 64), (32, 16), (16, 32),
+                               (22, 23), (27, 26), (32, 24), (29, 28), (17, 2), (2, 31)])
 @pytest.mark.parametrize("p,k", [(1, 1), (3, 5), (3, 25)])
 def test_fit_edges(kbl, monkeypatch, n, p, k):  # noqa: F811
     N = 5
@@ -33,7 +35,7 @@ def test_fit_edges(kbl, monkeypatch, n, p, k):  # noqa: F811
     wl.rowptr = np.arange(0, N * N * k + 1, k).astype(np.int32)
     wl.grid = GridSpec(GRID_STENCIL, n, k=4.0)
     print(f"[fit] grid {n} states {k * wl.n_s}", flush=True)
-    tile, plain = (11, 2) if max(n) <= 48 else (12, 5)
+    tile, plain = (1, 10) if max(n) <= 32 else (11, 2) if max(n) <= 48 else (12, 5)
     b, s = run(kbl, monkeypatch, wl, tile)
     rb, rs = oracle.workload_bounds(wl)
     full, fs = run(kbl, monkeypatch, wl, plain)
