@@ -115,7 +115,7 @@ __global__ __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(bwd_wav
     const BoundsArgs& p = a.f;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wid = tid >> 6;
-    const int bx = FIT ? (p.nx + TX - 1) / TX : BX;
+    const int bx = FIT ? split_threads(p.nx, TX) : BX;
     const int tx = tid % bx, ty = tid / bx;
     const double rm = 1.0 - p.r_fac, rp = 1.0 + p.r_fac;
     const int64_t nslot = p.nnz * p.n_s;

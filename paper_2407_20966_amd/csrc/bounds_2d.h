@@ -31,10 +31,13 @@ __attribute__((amdgpu_waves_per_eu(FIT ? (TX * TY <= 3 ? 5 : TX * TY <= 6 ? 4 : 
     __shared__ Red red;
 
     const int tid = threadIdx.x;
-    const int bx = FIT ? (p.nx + TX - 1) / TX : BX;
-    const int by = FIT ? (p.ny + TY - 1) / TY : BY;
+    const int bx = FIT ? split_threads(p.nx, TX) : BX;
+    const int by = FIT ? split_threads(p.ny, TY) : BY;
     const bool idle = FIT && tid >= bx * by;
     const int tx = idle ? 0 : tid % bx, ty = idle ? 0 : tid / bx;
+    // table columns of this thread's nodes
+    auto xcol = [&](int i) { return FIT ? split_column<FIT ? FIT : 1, TX>(tx + bx * i) : tx + bx * i; };
+    auto ycol = [&](int j) { return FIT ? split_column<FIT ? FIT : 1, TY>(ty + by * j) : ty + by * j; };
     const double rm = 1.0 - p.r_fac, rp = 1.0 + p.r_fac;
     stage_exp_table<NT>(sExp);   // published by the prologue's barriers
 
@@ -129,11 +132,11 @@ __attribute__((amdgpu_waves_per_eu(FIT ? (TX * TY <= 3 ? 5 : TX * TY <= 6 ? 4 : 
                     double ca[TX], cai[TX], cb[TY];
 #pragma unroll
                     for (int i = 0; i < TX; ++i) {
-                        ca[i] = sA[0][tx + bx * i];
-                        cai[i] = sA[1][tx + bx * i];
+                        ca[i] = sA[0][xcol(i)];
+                        cai[i] = sA[1][xcol(i)];
                     }
 #pragma unroll
-                    for (int j = 0; j < TY; ++j) cb[j] = sB[0][ty + by * j];
+                    for (int j = 0; j < TY; ++j) cb[j] = sB[0][ycol(j)];
                     // The stencil's first state sets the envelopes (q is its
                     // own min and max) instead of comparing with +-inf:
                     // tri2m 152.0 -> 150.6 ms, bounds bitwise the same (v_min
@@ -146,11 +149,11 @@ __attribute__((amdgpu_waves_per_eu(FIT ? (TX * TY <= 3 ? 5 : TX * TY <= 6 ? 4 : 
                         double na[TX], nai[TX], nb[TY];
 #pragma unroll
                         for (int i = 0; i < TX; ++i) {
-                            na[i] = sA[2 * sn][tx + bx * i];
-                            nai[i] = sA[2 * sn + 1][tx + bx * i];
+                            na[i] = sA[2 * sn][xcol(i)];
+                            nai[i] = sA[2 * sn + 1][xcol(i)];
                         }
 #pragma unroll
-                        for (int j = 0; j < TY; ++j) nb[j] = sB[sn][ty + by * j];
+                        for (int j = 0; j < TY; ++j) nb[j] = sB[sn][ycol(j)];
 #pragma unroll
                         for (int i = 0; i < TX; ++i)
 #pragma unroll
@@ -174,11 +177,11 @@ __attribute__((amdgpu_waves_per_eu(FIT ? (TX * TY <= 3 ? 5 : TX * TY <= 6 ? 4 : 
                         double na[TX], nai[TX], nb[TY];
 #pragma unroll
                         for (int i = 0; i < TX; ++i) {
-                            na[i] = sA[2 * sn][tx + bx * i];
-                            nai[i] = sA[2 * sn + 1][tx + bx * i];
+                            na[i] = sA[2 * sn][xcol(i)];
+                            nai[i] = sA[2 * sn + 1][xcol(i)];
                         }
 #pragma unroll
-                        for (int j = 0; j < TY; ++j) nb[j] = sB[sn][ty + by * j];
+                        for (int j = 0; j < TY; ++j) nb[j] = sB[sn][ycol(j)];
 #pragma unroll
                         for (int i = 0; i < TX; ++i)
 #pragma unroll
@@ -203,8 +206,8 @@ __attribute__((amdgpu_waves_per_eu(FIT ? (TX * TY <= 3 ? 5 : TX * TY <= 6 ? 4 : 
                     if (BTAB == 2) {
 #pragma unroll
                         for (int i = 0; i < TX; ++i) {
-                            a[i] = sA[2 * s][tx + bx * i];
-                            ai[i] = sA[2 * s + 1][tx + bx * i];
+                            a[i] = sA[2 * s][xcol(i)];
+                            ai[i] = sA[2 * s + 1][xcol(i)];
                         }
                     } else {
                         const Coef c = sC[t0 + s];
@@ -218,7 +221,7 @@ __attribute__((amdgpu_waves_per_eu(FIT ? (TX * TY <= 3 ? 5 : TX * TY <= 6 ? 4 : 
                     }
                     if (BTAB) {
 #pragma unroll
-                        for (int j = 0; j < TY; ++j) b[j] = sB[s][ty + by * j];
+                        for (int j = 0; j < TY; ++j) b[j] = sB[s][ycol(j)];
                     } else {
                         const Coef c = sC[t0 + s];
 #pragma unroll

@@ -48,10 +48,13 @@ __attribute__((amdgpu_waves_per_eu(TX * TY >= 12 ? 2 : TX * TY == 9 ? 3 : 4))) v
     static_assert(NXM == NYM && NXM <= NT, "tables built by columns");
 
     const int tid = threadIdx.x;
-    const int bx = FIT ? (p.nx + TX - 1) / TX : BX;
-    const int by = FIT ? (p.ny + TY - 1) / TY : BY;
+    const int bx = FIT ? split_threads(p.nx, TX) : BX;
+    const int by = FIT ? split_threads(p.ny, TY) : BY;
     const bool idle = FIT && tid >= bx * by;
     const int tx = idle ? 0 : tid % bx, ty = idle ? 0 : tid / bx;
+    // table columns of this thread's nodes
+    auto xcol = [&](int i) { return FIT ? split_column<FIT ? FIT : 1, TX>(tx + bx * i) : tx + bx * i; };
+    auto ycol = [&](int j) { return FIT ? split_column<FIT ? FIT : 1, TY>(ty + by * j) : ty + by * j; };
     const double rm = 1.0 - p.r_fac, rp = 1.0 + p.r_fac;
     stage_exp_table<NT>(sExp);   // published by the prologue's barriers
 
@@ -125,11 +128,11 @@ __attribute__((amdgpu_waves_per_eu(TX * TY >= 12 ? 2 : TX * TY == 9 ? 3 : 4))) v
                     double ea[TX], hc[TX], eb[TY];
 #pragma unroll
                     for (int i = 0; i < TX; ++i) {
-                        ea[i] = sEA[0][tx + bx * i];
+                        ea[i] = sEA[0][xcol(i)];
                         hc[i] = hux[i] + cs;
                     }
 #pragma unroll
-                    for (int j = 0; j < TY; ++j) eb[j] = sEB[0][ty + by * j];
+                    for (int j = 0; j < TY; ++j) eb[j] = sEB[0][ycol(j)];
 #pragma unroll
                     for (int i = 0; i < TX; ++i)
 #pragma unroll
@@ -149,11 +152,11 @@ __attribute__((amdgpu_waves_per_eu(TX * TY >= 12 ? 2 : TX * TY == 9 ? 3 : 4))) v
                     double ea[TX], hc[TX], eb[TY];
 #pragma unroll
                     for (int i = 0; i < TX; ++i) {
-                        ea[i] = sEA[s][tx + bx * i];
+                        ea[i] = sEA[s][xcol(i)];
                         hc[i] = hux[i] + cs;
                     }
 #pragma unroll
-                    for (int j = 0; j < TY; ++j) eb[j] = sEB[s][ty + by * j];
+                    for (int j = 0; j < TY; ++j) eb[j] = sEB[s][ycol(j)];
 #pragma unroll
                     for (int i = 0; i < TX; ++i)
 #pragma unroll

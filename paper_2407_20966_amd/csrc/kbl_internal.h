@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "../../include/kbl.h"
+#include "thread_split.h"
 
 namespace kbl {
 
@@ -104,7 +105,7 @@ hipError_t launch_bounds_fp64_small(const BoundsArgs& a, int nodes_per_thread, h
 // Whether 256 threads with TX x TY nodes each cover the grid.
 template <int TX, int TY>
 inline bool tile_fits_grid(const BoundsArgs& a) {
-    return ((a.nx + TX - 1) / TX) * ((a.ny + TY - 1) / TY) <= 256;
+    return split_fits<TX, TY>(a.nx, a.ny);
 }
 // Grids within 48 x 48 that 256 threads cover with 2 x 3 nodes each, larger ones
 // that they cover with 3 x 4.
