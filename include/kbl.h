@@ -168,7 +168,7 @@ kbl_status kbl_compute_bounds_nodes(const kbl_params* params, int32_t dim, int64
  * (meant for measurements and tests; they override kbl_autotune_bounds):
  *   KBL_BOUNDS_TILE=<t>        FP64 tile configuration index of the 2D or 3D
  *                              kernel (ignored if it does not cover the
- *                              velocity grid)
+ *                              velocity grid or take the stencils)
  *   KBL_MIXED_TILE=<t>         mixed-precision tile configuration index
  *   KBL_PERSISTENT_BLOCKS=<g>  grid of g workgroups walking the elements
  *                              (0 = one workgroup per element, -k = k
@@ -205,6 +205,18 @@ int32_t kbl_autotune_bounds(const kbl_params* params, int32_t dim, int64_t n_ele
 
 /* Forgets every choice made by kbl_autotune_bounds. */
 void kbl_autotune_clear(void);
+
+/*
+ * kbl_bounds_launch - the launch that kbl_compute_bounds would choose now for
+ * such a call (kbl_compute_bounds_nodes: n_s = 1): an override from the
+ * environment, else a choice of kbl_autotune_bounds, else the default.
+ *   tile    out: index of the tile configuration (0 in 1D and for
+ *           KBL_FLAG_ENERGY_PERSTATE, which have one kernel per grid).
+ *   blocks  out: launch shape, as KBL_PERSISTENT_BLOCKS gives it.
+ * Reads no array and launches nothing.  Errors as kbl_compute_bounds.
+ */
+kbl_status kbl_bounds_launch(const kbl_params* params, int32_t dim, int64_t n_elem, int32_t n_s,
+                             int64_t nnz, const kbl_vgrid* vgrid, int32_t* tile, int64_t* blocks);
 
 /*
  * kbl_limit - coupled squeeze limiter (Sec. 3.4, eq. alpha and eq. limiter,

@@ -153,6 +153,10 @@ def _load():
         lib.kbl_autotune_bounds.restype = C.c_int32
         lib.kbl_autotune_clear.argtypes = []
         lib.kbl_autotune_clear.restype = None
+        lib.kbl_bounds_launch.argtypes = [C.POINTER(Params), C.c_int32, C.c_int64, C.c_int32,
+                                          C.c_int64, C.POINTER(VGrid), C.POINTER(C.c_int32),
+                                          C.POINTER(C.c_int64)]
+        lib.kbl_bounds_launch.restype = C.c_int
         lib.kbl_backward_workspace_bytes.argtypes = [C.c_int32, C.c_int64, C.c_int32, C.c_int64]
         lib.kbl_backward_workspace_bytes.restype = C.c_size_t
         lib.kbl_bounds_limit_backward.argtypes = [C.POINTER(Params), C.c_int32, C.c_int64,
@@ -189,6 +193,16 @@ def _load():
         lib.kbl_fr1d_step_dev.restype = C.c_int
         _lib = lib
     return _lib
+
+
+def bounds_launch(params: Params, dim: int, n_elem: int, n_s: int, nnz: int, vgrid: VGrid):
+    """(tile, blocks) that kbl_compute_bounds would choose now for such a call."""
+    tile, blocks = C.c_int32(), C.c_int64()
+    rc = lib().kbl_bounds_launch(C.byref(params), dim, n_elem, n_s, nnz, C.byref(vgrid),
+                                 C.byref(tile), C.byref(blocks))
+    if rc != KBL_OK:
+        raise KblError(rc, "kbl_bounds_launch")
+    return tile.value, blocks.value
 
 
 def lib():

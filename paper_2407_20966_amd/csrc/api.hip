@@ -165,14 +165,47 @@ hipError_t launch_bounds_any(const kbl::BoundsArgs& a, int dim, int prec, int ti
                                  : kbl::launch_bounds_mixed(a, prec, st, tile);
 }
 
-// Whether a tile index names a launch configuration that covers the grid.
+// Whether a tile index names a launch configuration that covers the grid and
+// takes the stencils (the culling kernels index a row's states in 32 bits).
 bool tile_fits(const kbl::BoundsArgs& a, int dim, int prec, int tile) {
-    if (dim == 3) return kbl::bounds_tile_fits_3d(tile, a.nx, a.ny, a.nz);
+    if (dim == 3) return kbl::bounds_tile_fits_3d(tile, a);
     if (dim != 2) return false;
-    return prec == KBL_PREC_FP64 ? kbl::bounds_tile_fits_2d(tile, a.nx, a.ny)
+    return prec == KBL_PREC_FP64 ? kbl::bounds_tile_fits_2d(tile, a)
                                  : kbl::mixed_tile_fits_2d(tile, a.nx, a.ny);
 }
 
+// The autotuned choice for this problem if there is one and it fits, else the
+// default (tile -1).  A choice made on a smaller mesh may not fit this one.
+TuneVal tuned_or_default(const kbl::BoundsArgs& a, int dim, int prec) {
+    TuneVal v;
+    if (tuned(tune_key(a, dim, prec), &v) && (v.tile < 0 || tile_fits(a, dim, prec, v.tile)))
+        return v;
+    return TuneVal{-1, a.grid_blocks};
+}
+
+// The launch of a bounds call: a tuning-knob override, else an autotuned choice,
+// else the default (tile -1).
+TuneVal choose_launch(const kbl::BoundsArgs& a, int dim, int prec) {
+    TuneVal v{-1, a.grid_blocks};
+    if (!a.energy_perstate) {
+        v = tuned_or_default(a, dim, prec);
+        if (const char* env = getenv(prec == KBL_PREC_FP64 ? "KBL_BOUNDS_TILE" : "KBL_MIXED_TILE"))
+            v.tile = atoi(env);
+        if (!tile_fits(a, dim, prec, v.tile)) v.tile = -1;
+    }
+    if (const char* env = getenv("KBL_PERSISTENT_BLOCKS")) v.blocks = atoll(env);
+    return v;
+}
+
+// Precisions and readings of the energy bounds that a dimension has.
+kbl_status check_precision(const kbl::BoundsArgs& a, int dim, int prec) {
+    if (prec != KBL_PREC_FP64 && prec != KBL_PREC_MIXED_BF16 && prec != KBL_PREC_MIXED_FP16 &&
+        prec != KBL_PREC_MIXED_FP32)
+        return KBL_ERR_UNSUPPORTED;
+    if (prec != KBL_PREC_FP64 && (dim != 2 || a.energy_perstate)) return KBL_ERR_UNSUPPORTED;
+    if (dim == 3 && a.energy_perstate) return KBL_ERR_UNSUPPORTED;
+    return KBL_OK;
+}
 
 // Shared body of kbl_compute_bounds (source units = elements of n_s nodes)
 // and kbl_compute_bounds_nodes (source units = single nodes).
@@ -187,30 +220,15 @@ kbl_status compute_bounds_impl(const kbl_params* params, int32_t dim, int64_t n_
     if (rc != KBL_OK) return rc;
     if (n_elem > 0 && !bounds) return KBL_ERR_ARG;
     const int prec = params->precision;
-    if (prec != KBL_PREC_FP64 && prec != KBL_PREC_MIXED_BF16 && prec != KBL_PREC_MIXED_FP16 &&
-        prec != KBL_PREC_MIXED_FP32)
-        return KBL_ERR_UNSUPPORTED;
-    if (prec != KBL_PREC_FP64 && (dim != 2 || a.energy_perstate)) return KBL_ERR_UNSUPPORTED;
-    if (dim == 3 && a.energy_perstate) return KBL_ERR_UNSUPPORTED;
+    rc = check_precision(a, dim, prec);
+    if (rc != KBL_OK) return rc;
     a.bounds = bounds;
     a.status = elem_status;
-    if (const char* env = getenv("KBL_PERSISTENT_BLOCKS")) a.grid_blocks = atoll(env);
-    if (a.energy_perstate) {
-        const hipError_t err = kbl::launch_bounds_fp64_energy(a, dim, (hipStream_t)stream);
-        return err == hipSuccess ? KBL_OK : KBL_ERR_HIP;
-    }
-    // launch choice: a tuning-knob override, else an autotuned choice, else the defaults
-    int tile = -1;
-    TuneVal tv;
-    if (tuned(tune_key(a, dim, prec), &tv)) {
-        tile = tv.tile;
-        a.grid_blocks = tv.blocks;
-    }
-    if (const char* env = getenv(prec == KBL_PREC_FP64 ? "KBL_BOUNDS_TILE" : "KBL_MIXED_TILE"))
-        tile = atoi(env);
-    if (const char* env = getenv("KBL_PERSISTENT_BLOCKS")) a.grid_blocks = atoll(env);
-    if (prec == KBL_PREC_FP64 && dim >= 2 && !tile_fits(a, dim, prec, tile)) tile = -1;
-    const hipError_t err = launch_bounds_any(a, dim, prec, tile, (hipStream_t)stream);
+    const TuneVal v = choose_launch(a, dim, prec);
+    a.grid_blocks = v.blocks;
+    const hipError_t err =
+        a.energy_perstate ? kbl::launch_bounds_fp64_energy(a, dim, (hipStream_t)stream)
+                          : launch_bounds_any(a, dim, prec, v.tile, (hipStream_t)stream);
     return err == hipSuccess ? KBL_OK : KBL_ERR_HIP;
 }
 
@@ -298,6 +316,30 @@ kbl_status kbl_compute_bounds_nodes(const kbl_params* params, int32_t dim, int64
                                     uint32_t* elem_status, void* stream) {
     return compute_bounds_impl(params, dim, n_elem, n_nodes, 1, nnz, states, rowptr, cols, vgrid,
                                bounds, elem_status, stream);
+}
+
+kbl_status kbl_bounds_launch(const kbl_params* params, int32_t dim, int64_t n_elem, int32_t n_s,
+                             int64_t nnz, const kbl_vgrid* vgrid, int32_t* tile, int64_t* blocks) {
+    static const double some = 0.0;     // stands for the arrays, which are not read
+    kbl::BoundsArgs a;
+    kbl_status rc = make_bounds_args(params, dim, n_elem, n_elem, n_s, nnz, &some,
+                                     (const int32_t*)&some, (const int32_t*)&some, vgrid,
+                                     kMax1DNodes, &a);
+    if (rc != KBL_OK) return rc;
+    if (!tile || !blocks) return KBL_ERR_ARG;
+    const int prec = params->precision;
+    rc = check_precision(a, dim, prec);
+    if (rc != KBL_OK) return rc;
+    TuneVal v = choose_launch(a, dim, prec);
+    if (v.tile < 0 && !a.energy_perstate) {
+        a.grid_blocks = v.blocks;
+        if (dim == 3) v.tile = kbl::bounds_default_tile_3d(a);
+        if (dim == 2 && prec == KBL_PREC_FP64) v.tile = kbl::bounds_default_tile_2d(a, &v.blocks);
+        if (dim == 2 && prec != KBL_PREC_FP64) v.tile = kbl::mixed_default_tile_2d(a.nx, a.ny, prec);
+    }
+    *tile = v.tile < 0 ? 0 : v.tile;
+    *blocks = v.blocks;
+    return KBL_OK;
 }
 
 int32_t kbl_autotune_bounds(const kbl_params* params, int32_t dim, int64_t n_elem, int32_t n_s,
@@ -522,11 +564,10 @@ kbl_status backward_impl(const kbl_params* params, int32_t dim, int64_t n_elem, 
         // recompute the forward bounds (same precision, same launch choice)
         fa.bounds = wb;
         fa.status = wst;
-        int tile = -1;
-        TuneVal tv;
+        const TuneVal tv = tuned_or_default(fa, dim, prec);
         kbl::BoundsArgs ta = fa;
-        if (tuned(tune_key(fa, dim, prec), &tv)) { tile = tv.tile; ta.grid_blocks = tv.blocks; }
-        err = launch_bounds_any(ta, dim, prec, tile, st);
+        ta.grid_blocks = tv.blocks;
+        err = launch_bounds_any(ta, dim, prec, tv.tile, st);
         if (err != hipSuccess) return KBL_ERR_HIP;
         fb = wb;
         fs = wst;

@@ -90,6 +90,7 @@ constexpr Tile2D kTiles2D[] = {
     KBL_TILE(16, 16, 4, 4, 3),   // 14: n <= 64, states culled block by block
 };
 #undef KBL_TILE
+constexpr int kCullTile2 = 14;
 constexpr int kNumTiles2D = sizeof(kTiles2D) / sizeof(kTiles2D[0]);
 
 // Defaults from a measured sweep: with A, A + l and B read from LDS tables
@@ -138,26 +139,27 @@ bool cull_pays(const BoundsArgs& a) {
 int bounds_tile_count_2d() { return kNumTiles2D; }
 int bounds_default_tile_2d(int nx, int ny) { return default_tile_2d(nx, ny); }
 
-bool bounds_tile_fits_2d(int tile, int nx, int ny) {
+int bounds_default_tile_2d(const BoundsArgs& a, int64_t* blocks) {
+    *blocks = a.grid_blocks;
+    if (!cull_pays(a)) return default_tile_2d(a.nx, a.ny);
+    // one element per wave on small meshes (less of a tail)
+    if (a.grid_blocks == -2 && a.n_elem < 65536) *blocks = 0;
+    return kCullTile2;
+}
+
+bool bounds_tile_fits_2d(int tile, const BoundsArgs& a) {
     if (tile < 0 || tile >= kNumTiles2D) return false;
     const Tile2D& t = kTiles2D[tile];
-    return nx <= t.bx * t.tx && ny <= t.by * t.ty;
+    return a.nx <= t.bx * t.tx && a.ny <= t.by * t.ty && (tile != kCullTile2 || bounds_cull_fits(a));
 }
 
 hipError_t launch_bounds_fp64(const BoundsArgs& a, int dim, hipStream_t stream, int tile) {
     if (a.n_elem == 0) return hipSuccess;
     if (dim == 2) {
-        if (tile < 0) {
-            if (cull_pays(a)) {
-                // one element per wave on small meshes (less of a tail)
-                BoundsArgs b = a;
-                if (a.grid_blocks == -2 && a.n_elem < 65536) b.grid_blocks = -1;
-                return launch_bounds_cull_2d(b, stream);
-            }
-            tile = default_tile_2d(a.nx, a.ny);
-        }
-        if (!bounds_tile_fits_2d(tile, a.nx, a.ny)) return hipErrorInvalidValue;
-        return kTiles2D[tile].fn(a, stream);
+        BoundsArgs b = a;
+        if (tile < 0) tile = bounds_default_tile_2d(a, &b.grid_blocks);
+        if (!bounds_tile_fits_2d(tile, a)) return hipErrorInvalidValue;
+        return kTiles2D[tile].fn(b, stream);
     }
     return launch_bounds_fp64_1d(a, stream);
 }

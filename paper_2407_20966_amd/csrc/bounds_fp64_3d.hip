@@ -363,10 +363,10 @@ bool cull_pays_3d(const BoundsArgs& a) {
 
 int bounds_tile_count_3d() { return kNumTiles3D; }
 
-bool bounds_tile_fits_3d(int tile, int nx, int ny, int nz) {
-    if (tile < 0 || tile >= kNumTiles3D || nz < 2) return false;
+bool bounds_tile_fits_3d(int tile, const BoundsArgs& a) {
+    if (tile < 0 || tile >= kNumTiles3D || a.nz < 2) return false;
     const Tile3D& t = kTiles3D[tile];
-    return nx <= t.bx * t.tx && ny <= t.by * t.ty;
+    return a.nx <= t.bx * t.tx && a.ny <= t.by * t.ty && (tile != kCullTile3 || bounds_cull_fits_3d(a));
 }
 
 // Defaults: a thread tile that keeps two waves per SIMD (up to 18 nodes per
@@ -382,11 +382,14 @@ int bounds_default_tile_3d(int nx, int ny, int nz) {
     return 4;
 }
 
+int bounds_default_tile_3d(const BoundsArgs& a) {
+    return cull_pays_3d(a) ? kCullTile3 : bounds_default_tile_3d(a.nx, a.ny, a.nz);
+}
+
 hipError_t launch_bounds_fp64_3d(const BoundsArgs& a, hipStream_t stream, int tile) {
     if (a.n_elem == 0) return hipSuccess;
-    if (tile < 0)
-        tile = cull_pays_3d(a) ? kCullTile3 : bounds_default_tile_3d(a.nx, a.ny, a.nz);
-    if (!bounds_tile_fits_3d(tile, a.nx, a.ny, a.nz)) return hipErrorInvalidValue;
+    if (tile < 0) tile = bounds_default_tile_3d(a);
+    if (!bounds_tile_fits_3d(tile, a)) return hipErrorInvalidValue;
     return kTiles3D[tile].fn(a, stream);
 }
 

@@ -116,7 +116,10 @@ hipError_t launch_bounds_fp64_energy(const BoundsArgs& a, int dim, hipStream_t s
 // d = 3: FP64 bounds over a 3D velocity grid (tile < 0: default for the grid).
 hipError_t launch_bounds_fp64_3d(const BoundsArgs& a, hipStream_t stream, int tile);
 int bounds_tile_count_3d();
-bool bounds_tile_fits_3d(int tile, int nx, int ny, int nz);
+bool bounds_tile_fits_3d(int tile, const BoundsArgs& a);
+// The tile taken without a choice (for the grid alone: among those that evaluate
+// every pair).
+int bounds_default_tile_3d(const BoundsArgs& a);
 int bounds_default_tile_3d(int nx, int ny, int nz);
 // The 2D kernel that culls states block by block (one wave per element).
 hipError_t launch_bounds_cull_2d(const BoundsArgs& a, hipStream_t stream);
@@ -125,7 +128,9 @@ bool bounds_cull_fits(const BoundsArgs& a);
 hipError_t launch_bounds_cull_3d(const BoundsArgs& a, hipStream_t stream);
 bool bounds_cull_fits_3d(const BoundsArgs& a);
 int bounds_tile_count_2d();
-bool bounds_tile_fits_2d(int tile, int nx, int ny);
+bool bounds_tile_fits_2d(int tile, const BoundsArgs& a);
+// The same in 2D; blocks: the launch shape it is taken with.
+int bounds_default_tile_2d(const BoundsArgs& a, int64_t* blocks);
 int mixed_tile_count();
 int bounds_default_tile_2d(int nx, int ny);
 int mixed_default_tile_2d(int nx, int ny, int precision);

@@ -1,0 +1,55 @@
+"""The launch that a bounds call chooses (kbl_bounds_launch; no device): which
+kernel the default rules pick on both sides of their thresholds."""
+
+import os
+
+import pytest
+
+from paper_2407_20966_amd import _lib as L
+
+CULL = {2: 14, 3: 9}
+INT32_MAX = 2**31 - 1
+
+
+@pytest.fixture(autouse=True)
+def plain_environment(monkeypatch):
+    if not os.path.exists(L.LIB_PATH):
+        pytest.skip("libkbl.so not built (run __graft_entry__.build())")
+    for k in ("KBL_BOUNDS_TILE", "KBL_MIXED_TILE", "KBL_PERSISTENT_BLOCKS"):
+        monkeypatch.delenv(k, raising=False)
+
+
+def launch(n, n_elem, n_s, states, precision=L.PREC_FP64, flags=0):
+    """(tile, blocks) for rows of `states` states."""
+    p = L.Params()
+    L.lib().kbl_default_params(p, 1.4)
+    p.precision, p.flags = precision, flags
+    g = L.VGrid()
+    g.mode, g.k = L.GRID_STENCIL, 4.0
+    for i, m in enumerate(n):
+        g.n[i] = m
+    return L.bounds_launch(p, len(n), n_elem, n_s, states // n_s * n_elem, g)
+
+
+@pytest.mark.parametrize("n", [(64, 64), (40, 40, 40)])
+def test_culling_kernel_only_where_it_takes_the_rows(monkeypatch, n):
+    """nnz n_s beyond 2^31 - 1 or 2^16 nodes per element: asked for or not, the
+    culling kernel gives way to one that takes them."""
+    cull = CULL[len(n)]
+    n_s, states = 8, 56
+    at_most = INT32_MAX // states
+    for forced in (False, True):
+        if forced:
+            monkeypatch.setenv("KBL_BOUNDS_TILE", str(cull))
+        assert launch(n, at_most, n_s, states)[0] == cull
+        assert launch(n, at_most + 1, n_s, states)[0] != cull
+        assert launch(n, 4000, 65536, 65536)[0] != cull
+
+
+def test_errors_are_those_of_the_call():
+    with pytest.raises(L.KblError) as e:
+        launch((65, 64), 10, 1, 5)
+    assert e.value.code == L.KBL_ERR_GRID
+    with pytest.raises(L.KblError) as e:
+        launch((24, 24, 24), 10, 1, 7, precision=L.PREC_MIXED_FP32)
+    assert e.value.code == L.KBL_ERR_UNSUPPORTED
