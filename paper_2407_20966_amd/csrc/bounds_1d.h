@@ -51,8 +51,8 @@ struct Sums1D {
 // is largest at c,
 //   q_i - q_r <= (q_i - q_r)(c) + w |dg| + w^2 max(nk_i - nk_r, 0),
 // and a state for which that plus max(l_i - l_r, 0) is negative is neither
-// maximum; likewise from below.  Half widths and thresholds are widened by
-// 1e-10, far above rounding, so the envelopes are those of all states.
+// maximum; likewise from below.  Half widths are widened by 1e-10 and thresholds by
+// 1e-12, far above rounding, so the envelopes are those of all states.
 // 64 / 2^lg rounds from `round` on at once: lane = (round, state mod 2^lg).
 // Returns their masks side by side; the mask of a round past the grid is 0.
 template <int NT, int T>
@@ -71,9 +71,12 @@ __device__ __forceinline__ unsigned long long cull_1d(const BoundsArgs& p, const
     const Coef c = sC[live ? s : 0];
     const double d = cx - c.ux, t = c.nk * d, v = fma(t, d, c.a), qn = Q * c.nk;
     const double l = internal ? c.al - c.a : 0.0;
-    // the state's index in the low bits: the reference found is the extremum
-    // up to 2^-17 relative, and any state is a valid reference
-    const float key = __int_as_float((__float_as_int((float)v) & ~63) | s);
+    // q less the first state's, the state's index in the low bits: the reference
+    // found is the extremum up to 2^-17 of the states' spread, however little they
+    // differ, and any state is a valid reference
+    const Coef f = sC[0];
+    const double d0 = cx - f.ux, v0 = fma(f.nk * d0, d0, f.a);
+    const float key = __int_as_float((__float_as_int((float)(v - v0)) & ~63) | s);
     float kmax = live ? key : -kInfF, kmin = live ? key : kInfF;
     auto dpp = [](float x, auto ctrl) {
         return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x),
@@ -97,11 +100,12 @@ __device__ __forceinline__ unsigned long long cull_1d(const BoundsArgs& p, const
         const Coef r = sC[__float_as_int(side ? kmin : kmax) & 63];
         const double dr = cx - r.ux, tr = r.nk * dr, vr = fma(tr, dr, r.a), qr = Q * r.nk;
         const double lr = internal ? r.al - r.a : 0.0;
-        const double slack = 1e-10 * (1.0 + fabs(vr) + fabs(r.a) + w * fabs(tr) + fabs(qr) + fabs(lr));
+        const double slack = 1e-12 * (1.0 + fabs(vr) + fabs(r.a) + w * fabs(tr) + fabs(qr) + fabs(lr));
         const double sg = side ? -1.0 : 1.0;
         const double b = fma(w, fabs(t - tr), sg * (v - vr)) + fmax(sg * (l - lr), 0.0) +
                          fmax(sg * (qn - qr), 0.0);
-        keep = keep || b >= -slack;
+        // no finite bound (a denormal temperature): kept
+        keep = keep || !finite_bits(b) || b >= -slack;
     }
     return __builtin_amdgcn_ballot_w64(keep && live && ja < p.nx);
 }

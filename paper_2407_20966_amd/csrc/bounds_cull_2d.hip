@@ -19,7 +19,11 @@
 //       nk = -1 / (2 theta),  l = ln(theta delta / 2),
 //     staged in LDS, and the velocity box of eq. truncdomain.
 //  2. Cull, lane = block, two loops over the states.  The first finds the
-//     state r+ (r-) whose q is largest (smallest) at the block's centre.  The
+//     state r+ (r-) whose q is largest (smallest) at the block's centre, from the
+//     differences to the first state's q in FP32 (the values themselves, in
+//     FP32, tell states apart down to 2^-15 only; with references found so,
+//     flows that vary less within a stencil kept most states: 40000 quads of 80
+//     states that differ by 1e-6 took 4.0 ms on 64 x 64 nodes, 1.9 now).  The
 //     second bounds q_i - q_r over the block: with the half widths wx, wy and
 //     the gradients 2 nk (c - U) at the centre c,
 //       q_i - q_r <= (q_i - q_r)(c) + wx |dgx| + wy |dgy|
@@ -49,8 +53,8 @@
 // against 2.9 ms.  Four waves per SIMD (128 VGPRs) spilled in the loops and
 // ran 25% slower.
 //
-// Rounding: the bounds of step 2 are computed in FP64 with half widths and
-// thresholds widened by 1e-10 relative, far above their rounding error.
+// Rounding: the bounds of step 2 are computed in FP64, half widths widened by 1e-10
+// and thresholds by 1e-12 relative, far above their rounding error.
 #include <type_traits>
 
 #include "bounds_common.h"
@@ -160,6 +164,7 @@ __attribute__((amdgpu_waves_per_eu(3))) void bounds_cull_2d(BoundsArgs p, CullGr
 
         // ---- 1. prologue
         uint32_t bad = 0;
+        bool cold = false;
         double ext[8] = {kInf, kInf, kInf, kInf, 0.0, 0.0, 0.0, 0.0};
         for (int s = lane; s < S; s += 64) {
             CullState st;
@@ -167,6 +172,7 @@ __attribute__((amdgpu_waves_per_eu(3))) void bounds_cull_2d(BoundsArgs p, CullGr
             bad |= b;
             if (b) continue;
             if (s < kCullCap) L.rec[s] = st.r;
+            cold |= !finite_bits(st.r.nk);
             const double sd = sqrt(st.th);
             ext[0] = fmin(ext[0], box_lo(st.r.ux, p.k, sd));
             ext[1] = fmin(ext[1], -box_hi(st.r.ux, p.k, sd));
@@ -191,6 +197,8 @@ __attribute__((amdgpu_waves_per_eu(3))) void bounds_cull_2d(BoundsArgs p, CullGr
         const double hx = (hix - lox) / (double)(p.nx - 1);
         const double hy = (hiy - loy) / (double)(p.ny - 1);
         const bool big = S > kCullCap;
+        // no bounds of q without a finite nk (a denormal temperature)
+        const bool all = big || __ballot(cold) != 0;
         // velocity nodes and trapezoid weights
 #pragma unroll
         for (int d = 0; d < 2; ++d) {
@@ -205,8 +213,8 @@ __attribute__((amdgpu_waves_per_eu(3))) void bounds_cull_2d(BoundsArgs p, CullGr
         wave_lds_fence();
 
         // ---- 2. cull: lane = block
-        int cm = S, cn = S;              // list lengths: upper, lower envelopes
-        if (!big) {
+        int cm = 0, cn = 0;              // list lengths: upper, lower envelopes; 0: all states
+        if (!all) {
             const int x0 = bx * 2 * cg.hw, y0 = by * 2 * cg.hh;
             const double xa = L.node[0][x0 < 64 ? x0 : 63].u;
             const double xb = L.node[0][x0 + 2 * cg.hw - 1 < 64 ? x0 + 2 * cg.hw - 1 : 63].u;
@@ -218,19 +226,26 @@ __attribute__((amdgpu_waves_per_eu(3))) void bounds_cull_2d(BoundsArgs p, CullGr
             const double wy = (yb - ya) * (1.0 + 1e-10) + 1e-14 * (fabs(ya) + fabs(yb));
             const double Q = 0.25 * (wx * wx + wy * wy);
             float kmax = -kInfF, kmin = kInfF;
+            double v0;                   // q of the first state
+            {
+                const CullRec& r = L.rec[0];
+                const double dx = cx - r.ux, dy = cy - r.uy;
+                v0 = fma(r.nk, fma(dx, dx, dy * dy), r.a);
+            }
 #pragma unroll 4
             for (int s = 0; s < S; ++s) {
                 const CullRec& r = L.rec[s];
                 const double dx = cx - r.ux, dy = cy - r.uy;
-                const double v = fma(r.nk * dx, dx, fma(r.nk * dy, dy, r.a));
-                // the index in the low byte of the rounded value: the state
-                // found is the extremum up to 2^-15 relative, and any state
-                // is a valid reference
+                const double v = fma(r.nk, fma(dx, dx, dy * dy), r.a - v0);
+                // the index in the low byte of the rounded difference: the state
+                // found is the extremum up to 2^-15 of the states' spread (any
+                // state is a valid reference)
                 const float key = __int_as_float((__float_as_int((float)v) & ~255) | s);
                 kmax = fmaxf(kmax, key);
                 kmin = fminf(kmin, key);
             }
             double vr[2], tr[2], sr[2], lr[2], qr[2];
+            bool finite = true;
 #pragma unroll
             for (int side = 0; side < 2; ++side) {
                 const int ref = __float_as_int(side ? kmin : kmax) & 127;
@@ -240,15 +255,14 @@ __attribute__((amdgpu_waves_per_eu(3))) void bounds_cull_2d(BoundsArgs p, CullGr
                 sr[side] = r.nk * dy;
                 const double v = fma(tr[side], dx, fma(sr[side], dy, r.a));
                 qr[side] = Q * r.nk;
-                const double slack = 1e-10 * (1.0 + fabs(v) + fabs(r.a) + wx * fabs(tr[side]) +
+                const double slack = 1e-12 * (1.0 + fabs(v) + fabs(r.a) + wx * fabs(tr[side]) +
                                               wy * fabs(sr[side]) + fabs(qr[side]) + fabs(r.l));
+                finite = finite && finite_bits(slack);
                 lr[side] = r.l;
                 vr[side] = (side ? v + slack : v - slack) + (r.l + qr[side]);
             }
             uint8_t* const row0p = L.list[0][lane];
             uint8_t* const row1p = L.list[1][lane];
-            cm = 0;
-            cn = 0;
 #pragma unroll 4
             for (int s = 0; s < S; ++s) {
                 const CullRec& r = L.rec[s];
@@ -266,19 +280,21 @@ __attribute__((amdgpu_waves_per_eu(3))) void bounds_cull_2d(BoundsArgs p, CullGr
                 if (an) row1p[cn < kCullRow ? cn : kCullRow - 1] = (uint8_t)s;
                 cn += an ? 1 : 0;
             }
+            cm = finite ? cm : 0;
+            cn = finite ? cn : 0;
         }
 
         // ---- 3. blocks in ascending order of list length
-        const int em = cm > kCullRow ? S : cm, en = cn > kCullRow ? S : cn;
+        const int em = cm == 0 || cm > kCullRow ? S : cm, en = cn == 0 || cn > kCullRow ? S : cn;
         int order;                       // lane i: block and lengths at place i
         {
             int key = em + en;
             key = key < 32 ? key : (32 + (key - 32) / 8 < 63 ? 32 + (key - 32) / 8 : 63);
             if (!is_block) key = 0;      // sorted first (real blocks have key >= 2)
-            if (big) key = is_block ? 1 : 0;
+            if (all) key = is_block ? 1 : 0;
             unsigned v = (unsigned)key | ((unsigned)lane << 6) |
-                         ((unsigned)(cm > kCullRow || big ? 0 : cm) << 12) |
-                         ((unsigned)(cn > kCullRow || big ? 0 : cn) << 20);
+                         ((unsigned)(cm > kCullRow ? 0 : cm) << 12) |
+                         ((unsigned)(cn > kCullRow ? 0 : cn) << 20);
             static_assert(kCullRow < 256, "list lengths take 8 bits");
 #pragma unroll
             for (int b = 0; b < 6; ++b) {

@@ -1,0 +1,70 @@
+"""Culling kernels on flows that vary little within a stencil: the bounds are those of
+the oracle, and a variation of 1e-6 is culled as a variation of 1e-2 is (the
+time of the call says so)."""
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from synth.workloads import GRID_STENCIL, GridSpec
+from tests._parity import bounds_error, stencil_momentum_scale
+from tests.test_gpu_cull import TOL, kbl, run  # noqa: F401
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+GRIDS = {1: (1100,), 2: (40, 40), 3: (24, 18, 20)}
+TILE = {1: 0, 2: 14, 3: 9}
+
+
+def workload(dim, n, eps):
+    """Smooth periodic fields of relative amplitude eps around one state."""
+    make = {1: lambda: synth.make_line_workload(n_elem=n, seed=75, name="amp1"),
+            2: lambda: synth.make_quad_workload(N=n, p=2, seed=76, grid_nodes=16, name="amp2"),
+            3: lambda: synth.make_hex_workload(N=n, p=2, seed=77, grid_nodes=8, name="amp3")}
+    wl = make[dim]()
+    x = np.arange(wl.n_nodes) / wl.n_nodes
+    wave = [1.0 + eps * np.sin(2.0 * np.pi * (k + 3) * n * x + k) for k in range(dim + 2)]
+    rho, P = 1.3 * wave[0], 0.9 * wave[1]
+    U = [(0.4 - 0.3 * d) * wave[2 + d] for d in range(dim)]
+    wl.states = np.stack([rho] + [rho * u for u in U]
+                         + [P / (wl.gamma - 1.0) + 0.5 * rho * sum(u * u for u in U)])
+    wl.grid = GridSpec(GRID_STENCIL, GRIDS[dim], k=8.0 if dim == 1 else 4.0)
+    return wl
+
+
+@pytest.mark.parametrize("eps", [1e-16, 1e-14, 1e-12, 1e-9, 1e-6, 1e-4])
+@pytest.mark.parametrize("dim", [1, 2, 3])
+def test_small_amplitudes(kbl, monkeypatch, dim, eps):  # noqa: F811
+    wl = workload(dim, {1: 12, 2: 5, 3: 3}[dim], eps)
+    print(f"[amplitude] {dim}D {eps:g}", flush=True)
+    b, s = run(kbl, monkeypatch, wl, TILE[dim])
+    rb, rs = oracle.workload_bounds(wl)
+    assert np.array_equal(s, rs)
+    assert bounds_error(b, rb, dim, stencil_momentum_scale(wl))[0] <= TOL
+
+
+@pytest.mark.parametrize("dim,n", [(2, 100), (3, 14)])
+def test_small_amplitudes_are_culled(kbl, monkeypatch, dim, n):  # noqa: F811
+    monkeypatch.setenv("KBL_BOUNDS_TILE", str(TILE[dim]))
+    dev = torch.device("cuda:0")
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)
+    us = {}
+    for eps in (1e-2, 1e-6):
+        wl = workload(dim, n, eps)
+        vg = kbl.make_vgrid(wl.grid.mode, wl.grid.n[:dim], wl.grid.lo, wl.grid.hi, wl.grid.k)
+        prm = kbl.make_params(wl.gamma, r_fac=wl.r_fac)
+        args = (t(wl.states), t(wl.rowptr), t(wl.cols), wl.n_s, vg, prm)
+        times = []
+        for _ in range(8):
+            e0, e1 = torch.cuda.Event(True), torch.cuda.Event(True)
+            e0.record()
+            for _ in range(5):
+                kbl.compute_bounds(*args)
+            e1.record()
+            e1.synchronize()
+            times.append(e0.elapsed_time(e1) * 200.0)
+        us[eps] = min(times)
+    print(f"[amplitude] {dim}D {us}", flush=True)
+    assert us[1e-6] <= 1.35 * us[1e-2]
