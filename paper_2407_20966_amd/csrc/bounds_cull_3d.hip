@@ -119,7 +119,7 @@ __attribute__((amdgpu_waves_per_eu(3))) void bounds_cull_3d(BoundsArgs p, CullGr
             if (tid == 0) store_nan<3>(p, e, KBL_ST_BAD_STENCIL);
             continue;
         }
-        const int S = (int)(row1 - row0) * p.n_s;
+        int S = (int)(row1 - row0) * p.n_s;
 
         // ---- prologue
         uint32_t bad = 0;
@@ -145,7 +145,8 @@ __attribute__((amdgpu_waves_per_eu(3))) void bounds_cull_3d(BoundsArgs p, CullGr
         const double m = wave_transpose8<OpMin>(ext);
         if ((lane & 7) == 0) red.v[wid][lane >> 3] = m;
         __syncthreads();
-        if (bad || cold) atomicOr(&red.flags, bad | (cold ? kCold : 0u));
+        bad |= cold ? kCold : 0u;
+        if (bad) atomicOr(&red.flags, bad);
         // velocity nodes and trapezoid weights: wave j forms direction j
         if (wid < 3) {
             double lo = wid == 0 ? p.lo0 : wid == 1 ? p.lo1 : p.lo2;
@@ -213,7 +214,7 @@ __attribute__((amdgpu_waves_per_eu(3))) void bounds_cull_3d(BoundsArgs p, CullGr
                     w[d] = (ub - ua) * (1.0 + 1e-10) + 1e-14 * (fabs(ua) + fabs(ub));
                     Q = fma(0.25 * w[d], w[d], Q);
                 }
-                float kmax = -kInfF, kmin = kInfF;
+                float kmax = 0.f, kmin = 0.f;
                 double v0;               // q of the first state
                 {
                     const Rec3& r = L.rec[0];
@@ -221,7 +222,7 @@ __attribute__((amdgpu_waves_per_eu(3))) void bounds_cull_3d(BoundsArgs p, CullGr
                     v0 = fma(r.nk, fma(dx, dx, fma(dy, dy, dz * dz)), r.a);
                 }
 #pragma unroll 4
-                for (int s = 0; s < S; ++s) {
+                for (int s = 1; s < S; ++s) {
                     const Rec3& r = L.rec[s];
                     const double dx = c[0] - r.ux, dy = c[1] - r.uy, dz = c[2] - r.uz;
                     const double v = fma(r.nk, fma(dx, dx, fma(dy, dy, dz * dz)), r.a - v0);
@@ -233,7 +234,7 @@ __attribute__((amdgpu_waves_per_eu(3))) void bounds_cull_3d(BoundsArgs p, CullGr
                     kmin = fminf(kmin, key);
                 }
                 double vr[2], tr[2][3], lr[2], qr[2];
-                bool finite = true;
+                double slacks = 0.0;
 #pragma unroll
                 for (int sd = 0; sd < 2; ++sd) {
                     const Rec3 r = L.rec[__float_as_int(sd ? kmin : kmax) & 255];
@@ -247,7 +248,7 @@ __attribute__((amdgpu_waves_per_eu(3))) void bounds_cull_3d(BoundsArgs p, CullGr
                     const double slack = 1e-12 * (1.0 + fabs(v) + fabs(r.a) + w[0] * fabs(tr[sd][0]) +
                                                   w[1] * fabs(tr[sd][1]) + w[2] * fabs(tr[sd][2]) +
                                                   fabs(qr[sd]) + fabs(r.l));
-                    finite = finite && finite_bits(slack);
+                    slacks += slack;
                     vr[sd] = (sd ? v + slack : v - slack) + (r.l + qr[sd]);
                 }
                 // the rows' addresses are formed here (through an empty asm
@@ -280,8 +281,27 @@ __attribute__((amdgpu_waves_per_eu(3))) void bounds_cull_3d(BoundsArgs p, CullGr
                     if (an) row_l[cn < kRow ? cn : kRow - 1] = (uint8_t)s;
                     cn += an ? 1 : 0;
                 }
+                const bool finite = finite_bits(slacks);
                 cm = finite ? cm : 0;
                 cn = finite ? cn : 0;
+                if (__ballot(cm + cn < 2 * S) == 0) {
+                    // every block keeps every state: all may be the same (a constant
+                    // field), and the first then stands for all.  Every wave comes
+                    // here then and finds so.  (4096 hexahedra of 189 equal states on
+                    // 24^3 nodes: 0.66 ms, 3.1 with all evaluated.)
+                    const Rec3 f = L.rec[0];
+                    bool differs = false;
+                    for (int s = lane; s < S; s += 64) {
+                        const Rec3 r = L.rec[s];
+                        differs |= r.a != f.a || r.l != f.l || r.ux != f.ux || r.uy != f.uy ||
+                                   r.uz != f.uz || r.nk != f.nk;
+                    }
+                    if (__ballot(differs) == 0) {
+                        S = 1;
+                        cm = 0;
+                        cn = 0;
+                    }
+                }
             }
 
             // ---- blocks of the round in ascending order of list length: the

@@ -45,13 +45,13 @@ def test_small_amplitudes(kbl, monkeypatch, dim, eps):  # noqa: F811
     assert bounds_error(b, rb, dim, stencil_momentum_scale(wl))[0] <= TOL
 
 
-@pytest.mark.parametrize("dim,n", [(2, 100), (3, 14)])
-def test_small_amplitudes_are_culled(kbl, monkeypatch, dim, n):  # noqa: F811
+def timed(kbl, monkeypatch, dim, n, amplitudes):  # noqa: F811
+    """Time of a call per amplitude, in us."""
     monkeypatch.setenv("KBL_BOUNDS_TILE", str(TILE[dim]))
     dev = torch.device("cuda:0")
     t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)
     us = {}
-    for eps in (1e-2, 1e-6):
+    for eps in amplitudes:
         wl = workload(dim, n, eps)
         vg = kbl.make_vgrid(wl.grid.mode, wl.grid.n[:dim], wl.grid.lo, wl.grid.hi, wl.grid.k)
         prm = kbl.make_params(wl.gamma, r_fac=wl.r_fac)
@@ -67,4 +67,32 @@ def test_small_amplitudes_are_culled(kbl, monkeypatch, dim, n):  # noqa: F811
             times.append(e0.elapsed_time(e1) * 200.0)
         us[eps] = min(times)
     print(f"[amplitude] {dim}D {us}", flush=True)
+    return us
+
+
+@pytest.mark.parametrize("dim,n", [(2, 100), (3, 14)])
+def test_small_amplitudes_are_culled(kbl, monkeypatch, dim, n):  # noqa: F811
+    us = timed(kbl, monkeypatch, dim, n, (1e-2, 1e-6))
     assert us[1e-6] <= 1.35 * us[1e-2]
+
+
+def test_constant_stencils(kbl, monkeypatch):  # noqa: F811
+    """Constant fields, with one element of another state: bounds against the oracle,
+    and the time of a constant field is no more than that of a varying one."""
+    for dim in (1, 2, 3):
+        for odd in (False, True):
+            wl = workload(dim, {1: 12, 2: 5, 3: 3}[dim], 0.0)
+            wl.states = wl.states[:, :1] * np.ones_like(wl.states)
+            if odd:
+                wl.states[-1, 3 * wl.n_s + 1] *= 1.5
+            print(f"[amplitude] {dim}D constant, odd {odd}", flush=True)
+            b, s = run(kbl, monkeypatch, wl, TILE[dim])
+            rb, rs = oracle.workload_bounds(wl)
+            assert np.array_equal(s, rs)
+            assert bounds_error(b, rb, dim, stencil_momentum_scale(wl))[0] <= TOL
+
+
+@pytest.mark.parametrize("dim,n", [(1, 3000), (2, 100), (3, 14)])
+def test_constant_stencils_are_culled(kbl, monkeypatch, dim, n):  # noqa: F811
+    us = timed(kbl, monkeypatch, dim, n, (1e-2, 0.0))
+    assert us[0.0] <= us[1e-2]
