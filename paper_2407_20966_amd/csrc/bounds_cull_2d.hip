@@ -62,7 +62,6 @@
 namespace kbl {
 namespace {
 
-constexpr int kCullCap = 128;      // states staged per wave
 constexpr int kCullRow = 32;       // list entries per block and side
 
 struct CullGrid {

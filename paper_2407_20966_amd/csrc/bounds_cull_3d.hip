@@ -35,7 +35,7 @@
 namespace kbl {
 namespace {
 
-constexpr int kCap = 256;        // states staged at once
+constexpr int kCap = kCullCap3;  // states staged at once
 constexpr int kRow = 56;         // list entries per block and side
 
 struct CullGrid3 {

@@ -111,7 +111,7 @@ hipError_t launch_bounds_fp64_1d(const BoundsArgs& a, hipStream_t stream) {
     // a pass of the cull costs a wave about 80 ops, a state left out 16 per
     // round of 512 nodes: from two rounds and a dozen states on (below that the
     // plain kernel is 3-5% faster)
-    if (a.nx > 512 && a.nnz * a.n_s >= 10 * a.n_elem) return launch_1d<256, 2, true>(a, stream);
+    if (a.nx > 512 && states_at_least(a, 10)) return launch_1d<256, 2, true>(a, stream);
     return launch_1d<256, 2>(a, stream);
 }
 

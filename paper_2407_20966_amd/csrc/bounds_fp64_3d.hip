@@ -354,9 +354,23 @@ constexpr int kNumTiles3D = sizeof(kTiles3D) / sizeof(kTiles3D[0]);
 // tile 0's speed at 16^3 and 189 states); a few hundred elements do not fill
 // the chip, and its latency per element is the longer one unless the grid is
 // large (125 elements: 0.9 of the default tile at 24^3 nodes, 2.5 times at 64^3).
+// Stencils beyond the states it stages are evaluated in full there, at 0.77-0.79 of
+// tile 6's rate per node (264 to 729 states, 125 to 1000 elements) and at 1.0 of
+// tile 2's, so there the nodes decide that each covers: blocks of four in every
+// direction against 24 x 24 (slabs of 8) and 32 x 32 (of 2).  1.28-1.36 up to 20^3
+// nodes, 0.77-0.79 at 22^3 and 24^3, 1.05-1.3 at 25^3 and 28^3, 0.93-1.07 at 30^3,
+// 0.99-1.13 at 32^3; beyond 32 nodes 1.4-3.
 bool cull_pays_3d(const BoundsArgs& a) {
     const int n = a.nx > a.ny ? a.nx : a.ny;
-    return bounds_cull_fits_3d(a) && (n > 32 || (n > 16 && a.n_elem >= 512));
+    if (!bounds_cull_fits_3d(a)) return false;
+    if (n > 32) return true;
+    if (n <= 16 || a.n_elem < 512) return false;
+    if (!states_at_most(a, kCullCap3)) {
+        auto up = [](int m, int b) { return (m + b - 1) / b * b; };
+        const int own = up(a.nx, 4) * up(a.ny, 4) * up(a.nz, a.nz <= 32 ? 4 : 8);
+        return n <= 24 ? 4 * own <= 3 * (24 * 24 * up(a.nz, 8)) : own <= 32 * 32 * up(a.nz, 2);
+    }
+    return true;
 }
 
 }  // namespace

@@ -37,6 +37,10 @@ struct BoundsArgs {
                           // < 0 = -grid_blocks elements per workgroup
 };
 
+// Whether the rows hold at least / at most so many states on average.
+inline bool states_at_least(const BoundsArgs& a, int64_t s) { return a.nnz * a.n_s >= s * a.n_elem; }
+inline bool states_at_most(const BoundsArgs& a, int64_t s) { return a.nnz * a.n_s <= s * a.n_elem; }
+
 // Workgroups to launch for n_elem elements under a BoundsArgs::grid_blocks choice.
 inline unsigned bounds_grid(const BoundsArgs& a) {
     int64_t g = a.n_elem;
@@ -122,9 +126,11 @@ bool bounds_tile_fits_3d(int tile, const BoundsArgs& a);
 int bounds_default_tile_3d(const BoundsArgs& a);
 int bounds_default_tile_3d(int nx, int ny, int nz);
 // The 2D kernel that culls states block by block (one wave per element).
+constexpr int kCullCap = 128;        // states of a stencil it can cull
 hipError_t launch_bounds_cull_2d(const BoundsArgs& a, hipStream_t stream);
 bool bounds_cull_fits(const BoundsArgs& a);
 // The same for d = 3 (one workgroup per element).
+constexpr int kCullCap3 = 256;
 hipError_t launch_bounds_cull_3d(const BoundsArgs& a, hipStream_t stream);
 bool bounds_cull_fits_3d(const BoundsArgs& a);
 int bounds_tile_count_2d();

@@ -46,6 +46,25 @@ def test_culling_kernel_only_where_it_takes_the_rows(monkeypatch, n):
         assert launch(n, 4000, 65536, 65536)[0] != cull
 
 
+@pytest.mark.parametrize("n", [(40, 40), (50, 50), (64, 64)])
+def test_2d_stencils_beyond_the_staged_states(n):
+    for n_elem in (4096, 16384, 100000):
+        assert launch(n, n_elem, 16, 128)[0] == 14
+        for n_s, states in ((1, 129), (16, 144), (25, 225), (36, 180), (64, 320)):
+            assert launch(n, n_elem, n_s, states)[0] != 14
+
+
+def test_3d_stencils_beyond_the_staged_states():
+    # (nodes, kernel): 448 and 729 states, which no kernel can cull
+    for n, culls in (((18, 18, 18), True), ((20, 20, 20), True), ((22, 22, 22), False),
+                     ((24, 24, 24), False), ((28, 28, 28), True), ((30, 30, 30), False),
+                     ((40, 40, 40), True)):
+        for n_s, states in ((64, 448), (27, 729)):
+            assert (launch(n, 512, n_s, states)[0] == 9) == culls
+            assert (launch(n, 20000, n_s, states)[0] == 9) == culls
+        assert launch(n, 4096, 32, 256)[0] == 9
+
+
 def test_errors_are_those_of_the_call():
     with pytest.raises(L.KblError) as e:
         launch((65, 64), 10, 1, 5)
