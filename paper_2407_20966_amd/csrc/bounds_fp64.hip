@@ -125,10 +125,14 @@ int default_tile_2d(int nx, int ny) {
 // (30 x 30 to 64 x 64 nodes, 4096 and 16384 elements), 180 to 320 states 0.60-0.89;
 // 128 states 0.97-1.43.  Where rows of 110 and 140 alternate 0.78-1.0: the mean
 // is all that is known here.
+// With a handful of states there is little to leave out: 4 to 9 states 0.87-1.0 from
+// 3000 to 6400 elements (40 x 40 and 64 x 64 nodes), 13 and more 0.96-1.1; from 10000
+// on 0.98-1.16 with 4 to 9 too.
 bool cull_pays(const BoundsArgs& a) {
     if (!bounds_cull_fits(a) || !states_at_most(a, kCullCap)) return false;
     const int n = a.nx > a.ny ? a.nx : a.ny;
     if (n <= 24 || a.n_elem < 3000) return false;
+    if (a.n_elem < 8192 && !states_at_least(a, 12)) return false;
     if (n > 48) return true;
     if (n <= 32 && tile_fits_grid<1, 3>(a)) return false;
     const int hw = (a.nx + 15) / 16, hh = (a.ny + 15) / 16;

@@ -349,6 +349,18 @@ constexpr Tile3D kTiles3D[] = {
 constexpr int kCullTile3 = 9;
 constexpr int kNumTiles3D = sizeof(kTiles3D) / sizeof(kTiles3D[0]);
 
+// Whether there are too few states for the culling kernel to pay on grids where
+// tile 6 or 2 is the other default (512 to 4096 elements, times of the other over
+// those of the culling kernel):
+//   up to 20 nodes   7: 0.78-0.97   16: 0.9 at 512, 0.98-1.12 from 729 on   27: 1.0-1.27
+//   21 to 24         16: 0.76-0.92  27: 0.85 at 512, 0.9-1.03 beyond   56: 1.02-1.21
+//   25 to 32         7: 0.93-0.98 at 512, 1.02-1.22 beyond   16: 1.06-1.4
+bool few_states_3d(const BoundsArgs& a, int n) {
+    if (n <= 20) return !states_at_least(a, a.n_elem < 729 ? 24 : 12);
+    if (n <= 24) return !states_at_least(a, a.n_elem < 1728 ? 40 : 24);
+    return a.n_elem < 729 && !states_at_least(a, 12);
+}
+
 // Whether the culling kernel (tile 9) is the default.  Grids of up to 16 nodes
 // in x and y have blocks of a quarter of the box (lists of most states: 0.8 of
 // tile 0's speed at 16^3 and 189 states); a few hundred elements do not fill
@@ -364,7 +376,7 @@ bool cull_pays_3d(const BoundsArgs& a) {
     const int n = a.nx > a.ny ? a.nx : a.ny;
     if (!bounds_cull_fits_3d(a)) return false;
     if (n > 32) return true;
-    if (n <= 16 || a.n_elem < 512) return false;
+    if (n <= 16 || a.n_elem < 512 || few_states_3d(a, n)) return false;
     if (!states_at_most(a, kCullCap3)) {
         auto up = [](int m, int b) { return (m + b - 1) / b * b; };
         const int own = up(a.nx, 4) * up(a.ny, 4) * up(a.nz, a.nz <= 32 ? 4 : 8);

@@ -65,6 +65,23 @@ def test_3d_stencils_beyond_the_staged_states():
         assert launch(n, 4096, 32, 256)[0] == 9
 
 
+@pytest.mark.parametrize("n", [(40, 40), (50, 50), (64, 64)])
+def test_2d_few_states(n):
+    for states, n_s in ((5, 1), (9, 1), (4, 4)):
+        assert launch(n, 4096, n_s, states)[0] != 14
+        assert launch(n, 10000, n_s, states)[0] == 14
+    assert launch(n, 4096, 4, 20)[0] == 14
+    assert launch(n, 2025, 4, 20)[0] != 14
+
+
+@pytest.mark.parametrize("n,few,many", [(18, 7, 27), (24, 16, 56), (30, 7, 16)])
+def test_3d_few_states(n, few, many):
+    assert launch((n, n, n), 512, 1, few)[0] != 9
+    assert launch((n, n, n), 512, 1, many)[0] == 9
+    assert launch((n, n, n), 400, 1, many)[0] != 9
+    assert launch((40, 20, 20), 125, 1, few)[0] == 9
+
+
 def test_errors_are_those_of_the_call():
     with pytest.raises(L.KblError) as e:
         launch((65, 64), 10, 1, 5)
