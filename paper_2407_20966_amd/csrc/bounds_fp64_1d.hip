@@ -97,6 +97,57 @@ void bounds_fp64_1d(BoundsArgs p) {
     }
 }
 
+// Stencils beyond the staged states: all of a thread's nodes at once, so that every
+// chunk of states is staged once per element (in rounds of one node per thread
+// each chunk's logs are formed again in every round).  1000 stencils of 300
+// states: 172 us with 2048 nodes (296 in rounds), 54 with 300 (80), 29 with 40 (32).
+// Two waves per SIMD for eight nodes per thread: 186 us on 2048 nodes with three.
+template <int NT, int T>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(T < 8 ? 3 : T == 8 ? 2 : 1)))
+void bounds_fp64_1d_chunks(BoundsArgs p) {
+    __shared__ Coef sC[kMaxStates];
+    __shared__ ExpPair sExp[256];
+    __shared__ Red red;
+    const int tid = threadIdx.x;
+    const double rm = 1.0 - p.r_fac, rp = 1.0 + p.r_fac;
+    stage_exp_table<NT>(sExp);   // published by the prologue's barriers
+    for (ElemRange er = xcd_range(p.n_elem, p.grid_blocks); er.e < er.end; er.e += er.step) {
+        const int64_t e = er.e;
+        const int64_t row0 = p.rowptr[e], row1 = p.rowptr[e + 1];
+        if (row0 < 0 || row1 <= row0 || row1 > p.nnz) {
+            if (tid == 0) store_nan<1>(p, e, KBL_ST_BAD_STENCIL);
+            continue;
+        }
+        const int64_t S = (row1 - row0) * p.n_s;
+        double box[4];
+        const uint32_t flags = stencil_prologue<1, NT>(p, row0, S, red, sC, box);
+        if (flags & (KBL_ST_BAD_STENCIL | KBL_ST_INADMISSIBLE)) {
+            if (tid == 0) store_nan<1>(p, e, flags);
+            continue;
+        }
+        const double lo = box[0];
+        const double h = (box[1] - box[0]) / (double)(p.nx - 1);
+        Env1D<T> env;
+        for (int64_t c0 = 0; c0 < S; c0 += kMaxStates) {
+            const int cn = (int)((S - c0) < kMaxStates ? (S - c0) : kMaxStates);
+            if (c0 > 0) stage_chunk<1, NT>(p, row0, c0, cn, sC);
+            env.fold(p, sC, cn, lo, h, tid, NT, c0 == 0);
+        }
+        Sums1D sum1;
+        env.contract(p, lo, h, tid, NT, sExp, sum1);
+        double part[8];
+        sum1.parts(rm, rp, part);
+        const double sum = block_sum8<NT>(part, red);
+        if (tid < 6) store_bound_value<1>(p, e, tid, sum, flags);
+    }
+}
+
+template <int NT, int T>
+hipError_t launch_1d_chunks(const BoundsArgs& a, hipStream_t stream) {
+    hipLaunchKernelGGL((bounds_fp64_1d_chunks<NT, T>), dim3(bounds_grid(a)), dim3(NT), 0, stream, a);
+    return hipGetLastError();
+}
+
 template <int NT, int T, bool CULL = false>
 hipError_t launch_1d(const BoundsArgs& a, hipStream_t stream) {
     hipLaunchKernelGGL((bounds_fp64_1d<NT, T, CULL>), dim3(bounds_grid(a)), dim3(NT), 0, stream, a);
@@ -106,6 +157,15 @@ hipError_t launch_1d(const BoundsArgs& a, hipStream_t stream) {
 }  // namespace
 
 hipError_t launch_bounds_fp64_1d(const BoundsArgs& a, hipStream_t stream) {
+    // rows of both kinds take the rounds above, chunk by chunk where they must
+    if (!states_at_most(a, kMaxStates)) {
+        if (a.nx <= 64) return launch_1d_chunks<64, 1>(a, stream);
+        if (a.nx <= 256) return launch_1d_chunks<256, 1>(a, stream);
+        if (a.nx <= 512) return launch_1d_chunks<256, 2>(a, stream);
+        if (a.nx <= 1024) return launch_1d_chunks<256, 4>(a, stream);
+        if (a.nx <= 2048) return launch_1d_chunks<256, 8>(a, stream);
+        return launch_1d_chunks<256, 16>(a, stream);
+    }
     if (a.nx <= 64) return launch_1d<64, 1>(a, stream);
     if (a.nx <= 256) return launch_1d<256, 1>(a, stream);
     // a pass of the cull costs a wave about 80 ops, a state left out 16 per
