@@ -45,23 +45,6 @@ struct Sums1D {
     }
 };
 
-// The value of the first lane of an aligned group of 2^lg lanes (lg 4, 5 or 6).
-__device__ __forceinline__ double first_of_group(double v, int lg) {
-    const long long b = __double_as_longlong(v);
-    const int lo = (int)b, hi = (int)(b >> 32);
-    int l, h;
-    if (lg == 4) {
-        constexpr int kRowBcast0 = 0x150;       // row_newbcast:0
-        l = __builtin_amdgcn_update_dpp(0, lo, kRowBcast0, 0xF, 0xF, false);
-        h = __builtin_amdgcn_update_dpp(0, hi, kRowBcast0, 0xF, 0xF, false);
-    } else {
-        const bool second = lg == 5 && (threadIdx.x & 32);
-        l = second ? __builtin_amdgcn_readlane(lo, 32) : __builtin_amdgcn_readlane(lo, 0);
-        h = second ? __builtin_amdgcn_readlane(hi, 32) : __builtin_amdgcn_readlane(hi, 0);
-    }
-    return __longlong_as_double(((long long)h << 32) | (long long)(unsigned)l);
-}
-
 // Which of S <= 64 staged states can hold an extremum of g or g_I at the wave's
 // nodes of a round: the wave owns 64 T consecutive nodes of a round of NT T.
 // With c the middle of those nodes, w their half width and r the state whose q
@@ -91,7 +74,8 @@ __device__ __forceinline__ unsigned long long cull_1d(const BoundsArgs& p, const
     // q less the first state's, the state's index in the low bits: the reference
     // found is the extremum up to 2^-17 of the states' spread, however little they
     // differ, and any state is a valid reference
-    const double v0 = first_of_group(v, lg);
+    const Coef& f = sC[0];
+    const double d0 = cx - f.ux, v0 = fma(f.nk * d0, d0, f.a);
     const float key = __int_as_float((__float_as_int((float)(v - v0)) & ~63) | s);
     float kmax = live ? key : -kInfF, kmin = live ? key : kInfF;
     auto dpp = [](float x, auto ctrl) {
@@ -128,7 +112,6 @@ __device__ __forceinline__ unsigned long long cull_1d(const BoundsArgs& p, const
     if (keep == in_grid) {
         // every state is kept: where all are the same (a constant field) the first
         // stands for them
-        const Coef& f = sC[0];
         if (__builtin_amdgcn_ballot_w64(c.a != f.a || c.al != f.al || c.ux != f.ux || c.nk != f.nk) == 0)
             keep &= __builtin_amdgcn_ballot_w64(s == 0);
     }
