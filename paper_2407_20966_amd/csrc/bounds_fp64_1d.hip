@@ -23,8 +23,8 @@ namespace {
 // tie up to rounding all are visited in the plain loop, of equal states one is
 // (20000 stencils of 12 on 1100 nodes: 133 us, 195 with all, 254 before the cull).
 // The 1D solver's stencils of 6 to 12 states gain nothing by it.
-template <int NT, int T, bool CULL>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(5)))
+template <int NT, int T, bool CULL, int WAVES>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WAVES)))
 void bounds_fp64_1d(BoundsArgs p) {
     __shared__ Coef sC[kMaxStates];
     __shared__ ExpPair sExp[256];
@@ -148,9 +148,9 @@ hipError_t launch_1d_chunks(const BoundsArgs& a, hipStream_t stream) {
     return hipGetLastError();
 }
 
-template <int NT, int T, bool CULL = false>
+template <int NT, int T, bool CULL = false, int WAVES = 5>
 hipError_t launch_1d(const BoundsArgs& a, hipStream_t stream) {
-    hipLaunchKernelGGL((bounds_fp64_1d<NT, T, CULL>), dim3(bounds_grid(a)), dim3(NT), 0, stream, a);
+    hipLaunchKernelGGL((bounds_fp64_1d<NT, T, CULL, WAVES>), dim3(bounds_grid(a)), dim3(NT), 0, stream, a);
     return hipGetLastError();
 }
 
@@ -168,10 +168,26 @@ hipError_t launch_bounds_fp64_1d(const BoundsArgs& a, hipStream_t stream) {
     }
     if (a.nx <= 64) return launch_1d<64, 1>(a, stream);
     if (a.nx <= 256) return launch_1d<256, 1>(a, stream);
+    // Meshes of up to three workgroups per CU or so are bound by the latency of one
+    // workgroup's rounds, not by the waves in flight: all nodes in one round there, in
+    // the registers of fewer waves.  Up to 512 nodes, 3 to 18 states: 7.1-8.1 us at
+    // 500 to 700 elements against 7.2-8.7 in the five-wave form; from 768 on 128
+    // threads with four nodes each, 7.2-8.7 at 1000 elements against 7.9-9.8, 75 us at
+    // 20000 elements of 6 states against 93.
+    const bool few = a.n_elem < 768;
+    if (a.nx <= 512)
+        return few ? launch_1d<256, 2, false, 3>(a, stream) : launch_1d<128, 4, false, 3>(a, stream);
+    // Up to 1024 nodes likewise, unless the cull below is worth more: 12 states
+    // 6.8-8.4 us at 32 to 500 elements against 7.7-9.4 with it, 18 states 8.9 and
+    // 9.0-9.6, 30 states 10.8 and 10.2; at 850 elements 10 states 10.3 and 11.7, 12
+    // states 10.8 and 10.3-11.7.
+    if (a.nx <= 1024 && (few ? !states_at_least(a, 18)
+                             : a.n_elem < 1024 && !states_at_least(a, 12)))
+        return launch_1d<256, 4, false, 4>(a, stream);
     // a pass of the cull costs a wave about 80 ops, a state left out 16 per
     // round of 512 nodes: from two rounds and a dozen states on (below that the
     // plain kernel is 3-5% faster)
-    if (a.nx > 512 && states_at_least(a, 10)) return launch_1d<256, 2, true>(a, stream);
+    if (states_at_least(a, 10)) return launch_1d<256, 2, true>(a, stream);
     return launch_1d<256, 2>(a, stream);
 }
 

@@ -71,3 +71,10 @@ def test_stencils_beyond_the_staged_states_are_staged_once(kbl):  # noqa: F811
     us = {k: best_us(device_call(kbl, line(1000, 4, k, 2048, 310))) for k in (30, 60)}
     print(f"[1d] us by elements per stencil: {us}", flush=True)
     assert us[60] <= 2.0 * us[30]          # 300 and 150 states
+
+
+@pytest.mark.parametrize("nu", [257, 384, 385, 511, 512, 513, 768, 769, 1023, 1024])
+@pytest.mark.parametrize("n_elem", [40, 767, 768, 1023, 1024])
+def test_splits_by_mesh_size(kbl, n_elem, nu):  # noqa: F811
+    for p, k in ((2, 1), (2, 3), (3, 3), (5, 3)):      # 3, 9, 12 and 18 states
+        check(kbl, line(n_elem, p, k, nu, 320 + nu))
