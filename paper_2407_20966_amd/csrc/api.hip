@@ -83,7 +83,7 @@ kbl_status make_bounds_args(const kbl_params* params, int32_t dim, int64_t n_ele
     // below a thousand elements and a longer last round up to some thousands
     // (48 x 48 nodes, FP64: 144 elements 31 -> 17 us, 400 32 -> 23, 2025 73 -> 66,
     // 5625 173 -> 173, 10000 191 -> 193; FP32 400 35 -> 21, 2500 80 -> 70, 6400 167 ->
-    // 162, though 2025, where two fill the chip exactly once, 56 -> 60).
+    // 162).  The mixed forms have exceptions (mixed_default_blocks).
     a->grid_blocks = dim == 2 && n_elem >= kTwoPerWorkgroup ? -2 : 0;
     a->nx = g.n[0];
     a->ny = dim >= 2 ? g.n[1] : 1;
@@ -174,13 +174,19 @@ bool tile_fits(const kbl::BoundsArgs& a, int dim, int prec, int tile) {
                                  : kbl::mixed_tile_fits_2d(tile, a.nx, a.ny);
 }
 
+// The launch shape without a choice (tile < 0: of the default tile).
+int64_t default_blocks(const kbl::BoundsArgs& a, int dim, int prec, int tile) {
+    return dim == 2 && prec != KBL_PREC_FP64 ? kbl::mixed_default_blocks(a, prec, tile)
+                                             : a.grid_blocks;
+}
+
 // The autotuned choice for this problem if there is one and it fits, else the
 // default (tile -1).  A choice made on a smaller mesh may not fit this one.
 TuneVal tuned_or_default(const kbl::BoundsArgs& a, int dim, int prec) {
     TuneVal v;
     if (tuned(tune_key(a, dim, prec), &v) && (v.tile < 0 || tile_fits(a, dim, prec, v.tile)))
         return v;
-    return TuneVal{-1, a.grid_blocks};
+    return TuneVal{-1, default_blocks(a, dim, prec, -1)};
 }
 
 // The launch of a bounds call: a tuning-knob override, else an autotuned choice,
@@ -189,8 +195,10 @@ TuneVal choose_launch(const kbl::BoundsArgs& a, int dim, int prec) {
     TuneVal v{-1, a.grid_blocks};
     if (!a.energy_perstate) {
         v = tuned_or_default(a, dim, prec);
-        if (const char* env = getenv(prec == KBL_PREC_FP64 ? "KBL_BOUNDS_TILE" : "KBL_MIXED_TILE"))
+        if (const char* env = getenv(prec == KBL_PREC_FP64 ? "KBL_BOUNDS_TILE" : "KBL_MIXED_TILE")) {
+            if (v.tile < 0) v.blocks = default_blocks(a, dim, prec, atoi(env));
             v.tile = atoi(env);
+        }
         if (!tile_fits(a, dim, prec, v.tile)) v.tile = -1;
     }
     if (const char* env = getenv("KBL_PERSISTENT_BLOCKS")) v.blocks = atoll(env);

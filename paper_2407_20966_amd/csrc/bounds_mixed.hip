@@ -600,6 +600,31 @@ int default_mixed_tile(int nx, int ny, int precision) {
 }  // namespace
 
 int mixed_tile_count() { return kNumMixedTiles; }
+
+// Two elements per workgroup on large meshes (BoundsArgs::grid_blocks), one on
+// smaller ones, except where two do better there too (times of two over one, quads of
+// 20 and 80 states):
+//  - Two fill the chip's 256 CUs exactly once, where one leaves a second round partly
+//    empty: 0.89-0.92 at 3600 and 4096 elements on 16 x 16 nodes (1.05 at 3249,
+//    1.15-1.23 at 4624), 0.91-0.97 at 2025 on 48 x 48 (1.02-1.07 at 1764, 1.2-1.25 at
+//    2304), and with 80 states 0.92 and 0.96 at 2025 and 4096 on 64 x 64 with tile 5
+//    (1.05-1.07 with 20 states).  Later rounds are less regular: 1.05 at 4096 on 48 x 48.
+//  - Tile 6, whose set-up is the longest: 0.95-0.98 from 4096 to 6400 elements of 20
+//    states (0.96-1.07 from 2500 to 3600), with 80 states 0.97-1.0 in BF16 and 1.0-1.05 in
+//    FP32.
+int64_t mixed_default_blocks(const BoundsArgs& a, int precision, int tile) {
+    if (a.grid_blocks != 0) return a.grid_blocks;
+    if (tile < 0) tile = default_mixed_tile(a.nx, a.ny, precision);
+    const bool many = states_at_least(a, 40);
+    // elements per 128 CUs, rounded up
+    const int64_t n = (a.n_elem + 127) / 128;
+    bool two = false;
+    if (tile == 0) two = n > 26 && n <= 32;
+    if (tile == 4) two = n > 15 && n <= 16;
+    if (tile == 5) two = many && ((n > 15 && n <= 16) || (n > 30 && n <= 32));
+    if (tile == 6) two = n >= 32 && (precision == KBL_PREC_MIXED_BF16 || !many);
+    return two ? -2 : 0;
+}
 bool mixed_tile_fits_2d(int tile, int nx, int ny) { return mixed_tile_fits(tile, nx, ny); }
 int mixed_default_tile_2d(int nx, int ny, int precision) { return default_mixed_tile(nx, ny, precision); }
 

@@ -140,6 +140,8 @@ int bounds_default_tile_2d(const BoundsArgs& a, int64_t* blocks);
 int mixed_tile_count();
 int bounds_default_tile_2d(int nx, int ny);
 int mixed_default_tile_2d(int nx, int ny, int precision);
+// The launch shape without a choice (tile < 0: of the default tile).
+int64_t mixed_default_blocks(const BoundsArgs& a, int precision, int tile);
 bool mixed_tile_fits_2d(int tile, int nx, int ny);
 // tile < 0 (or a tile that does not fit) selects the default for the grid size.
 hipError_t launch_bounds_mixed(const BoundsArgs& a, int precision, hipStream_t stream, int tile);

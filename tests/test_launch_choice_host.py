@@ -82,6 +82,37 @@ def test_3d_few_states(n, few, many):
     assert launch((40, 20, 20), 125, 1, few)[0] == 9
 
 
+MIXED = (L.PREC_MIXED_BF16, L.PREC_MIXED_FP16, L.PREC_MIXED_FP32)
+
+
+@pytest.mark.parametrize("n,one,two", [((16, 16), (100, 3249, 4624, 8100), (3600, 4096, 8192, 10**6)),
+                                       ((32, 32), (2025, 4096, 8100), (8192, 10**6)),
+                                       ((48, 48), (1764, 2304, 4096, 8100), (2025, 2048, 8192)),
+                                       ((64, 64), (1764, 2304, 3249), (8192, 10**6))])
+def test_mixed_elements_per_workgroup(n, one, two):
+    for prec in MIXED:
+        for states in (16, 80):
+            assert all(launch(n, e, 16, states, prec)[1] == 0 for e in one)
+            assert all(launch(n, e, 16, states, prec)[1] == -2 for e in two)
+
+
+def test_mixed_elements_per_workgroup_by_tile(monkeypatch):
+    n = (64, 64)
+    for n_elem in (2025, 4096):
+        assert launch(n, n_elem, 16, 80, L.PREC_MIXED_FP16) == (5, -2)
+        assert launch(n, n_elem, 4, 20, L.PREC_MIXED_FP16) == (5, 0)
+        assert launch(n, n_elem + 200, 16, 80, L.PREC_MIXED_FP16) == (5, 0)
+    assert launch(n, 5000, 16, 80, L.PREC_MIXED_BF16) == (6, -2)
+    assert launch(n, 5000, 16, 80, L.PREC_MIXED_FP32) == (6, 0)
+    for prec in (L.PREC_MIXED_BF16, L.PREC_MIXED_FP32):
+        assert launch(n, 4096, 4, 20, prec) == (6, -2)
+        assert launch(n, 2025, 4, 20, prec) == (6, 0)
+    monkeypatch.setenv("KBL_MIXED_TILE", "6")
+    assert launch((48, 48), 2025, 16, 80, L.PREC_MIXED_FP32) == (6, 0)
+    monkeypatch.setenv("KBL_PERSISTENT_BLOCKS", "-4")
+    assert launch((48, 48), 2025, 16, 80, L.PREC_MIXED_FP32) == (6, -4)
+
+
 def test_errors_are_those_of_the_call():
     with pytest.raises(L.KblError) as e:
         launch((65, 64), 10, 1, 5)
