@@ -190,7 +190,9 @@ kbl_status kbl_compute_bounds_nodes(const kbl_params* params, int32_t dim, int64
  * each candidate keeps the better of two trials, and the default launch is
  * kept unless another candidate is more than 3% faster.
  * The choice is kept (per process) for later kbl_compute_bounds calls with
- * the same dimension, precision, grid size, nodes per element and grid mode.
+ * the same dimension, precision, grid size, nodes per element and grid mode, on
+ * meshes within a factor of two of its elements and a quarter of its states per
+ * element (which kernel is fastest depends on both; other meshes keep the default).
  * Synchronises `stream`; leaves the full bounds of all elements in `bounds`
  * (and the status in `elem_status` when non-null).  Returns 8 * tile + shape
  * for the chosen candidate (tile: index of the tile configuration, 0 in 1D;

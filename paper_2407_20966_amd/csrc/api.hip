@@ -132,7 +132,11 @@ kbl_status make_limit_args(const kbl_params* params, int32_t dim, int64_t n_elem
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // ---------------------------------------------------------------- autotune
-// Launch choices found by kbl_autotune_bounds, per problem shape.
+// Launch choices found by kbl_autotune_bounds, per problem shape.  The fastest kernel
+// depends on the elements and on the states per element too (by up to two times
+// between a few hundred elements and some thousands): each choice holds for meshes
+// within a factor of two of the tuned one's elements and a quarter of its mean
+// states, and of those that do the one with the nearest elements is taken.
 struct TuneKey {
     int dim, prec, nx, ny, nz, n_s, mode;
     bool operator<(const TuneKey& o) const {
@@ -144,19 +148,47 @@ struct TuneVal {
     int tile;            // tile configuration index
     int64_t blocks;      // BoundsArgs::grid_blocks of the choice
 };
+struct TuneEntry {
+    int64_t n_elem, nnz;
+    TuneVal v;
+};
+constexpr size_t kTuneEntries = 64;     // per shape; the oldest goes first
 std::mutex g_tune_mu;
-std::map<TuneKey, TuneVal> g_tune;
+std::map<TuneKey, std::vector<TuneEntry>> g_tune;
 
 TuneKey tune_key(const kbl::BoundsArgs& a, int dim, int prec) {
     return TuneKey{dim, prec, a.nx, a.ny, a.nz, a.n_s, a.grid_mode};
 }
 
-bool tuned(const TuneKey& k, TuneVal* v) {
+bool tuned(const TuneKey& k, int64_t n_elem, int64_t nnz, TuneVal* v) {
     std::lock_guard<std::mutex> lock(g_tune_mu);
     auto it = g_tune.find(k);
-    if (it == g_tune.end()) return false;
-    *v = it->second;
-    return true;
+    if (it == g_tune.end() || n_elem < 1) return false;
+    const double row = (double)nnz / (double)n_elem;
+    double best = 2.0;                  // ratio of the element counts, >= 1
+    bool found = false;
+    for (const TuneEntry& t : it->second) {
+        const double r = (double)n_elem / (double)t.n_elem, ratio = r < 1.0 ? 1.0 / r : r;
+        const double q = row * (double)t.n_elem / (double)t.nnz;
+        if (ratio > best || q > 1.25 || q < 0.8) continue;
+        best = ratio;
+        *v = t.v;
+        found = true;
+    }
+    return found;
+}
+
+// Keeps a choice, in the place of an earlier one for the same mesh size.
+void keep_tuned(const TuneKey& k, int64_t n_elem, int64_t nnz, const TuneVal& v) {
+    std::lock_guard<std::mutex> lock(g_tune_mu);
+    std::vector<TuneEntry>& es = g_tune[k];
+    for (size_t i = 0; i < es.size(); ++i)
+        if (es[i].n_elem == n_elem && es[i].nnz == nnz) {
+            es.erase(es.begin() + i);
+            break;
+        }
+    if (es.size() >= kTuneEntries) es.erase(es.begin());
+    es.push_back(TuneEntry{n_elem, nnz, v});
 }
 
 hipError_t launch_bounds_any(const kbl::BoundsArgs& a, int dim, int prec, int tile, hipStream_t st) {
@@ -184,7 +216,7 @@ int64_t default_blocks(const kbl::BoundsArgs& a, int dim, int prec, int tile) {
 // default (tile -1).  A choice made on a smaller mesh may not fit this one.
 TuneVal tuned_or_default(const kbl::BoundsArgs& a, int dim, int prec) {
     TuneVal v;
-    if (tuned(tune_key(a, dim, prec), &v) && (v.tile < 0 || tile_fits(a, dim, prec, v.tile)))
+    if (tuned(tune_key(a, dim, prec), a.n_elem, a.nnz, &v) && (v.tile < 0 || tile_fits(a, dim, prec, v.tile)))
         return v;
     return TuneVal{-1, default_blocks(a, dim, prec, -1)};
 }
@@ -439,10 +471,7 @@ int32_t kbl_autotune_bounds(const kbl_params* params, int32_t dim, int64_t n_ele
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (best_idx < 0) return -1;
-    {
-        std::lock_guard<std::mutex> lock(g_tune_mu);
-        g_tune[tune_key(a, dim, prec)] = bestv;
-    }
+    if (nnz > 0) keep_tuned(tune_key(a, dim, prec), n_elem, nnz, bestv);
     // leave the full result in `bounds`
     a.bounds = bounds;
     a.status = elem_status;

@@ -1,0 +1,50 @@
+"""What an autotuned choice is used for: meshes like the one it was made on, and
+no others."""
+
+import numpy as np
+import pytest
+
+import synth
+from synth.workloads import GRID_STENCIL, GridSpec
+from tests.test_gpu_cull import kbl  # noqa: F401
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def tensors(wl):
+    dev = torch.device("cuda:0")
+    return [torch.from_numpy(np.ascontiguousarray(a)).to(dev) for a in (wl.states, wl.rowptr, wl.cols)]
+
+
+def test_choice_holds_for_meshes_of_its_size(kbl, monkeypatch):  # noqa: F811
+    for k in ("KBL_BOUNDS_TILE", "KBL_MIXED_TILE", "KBL_PERSISTENT_BLOCKS"):
+        monkeypatch.delenv(k, raising=False)
+    wl = synth.make_quad_workload(N=120, seed=960, grid_nodes=64, name="tune")
+    wl.grid = GridSpec(GRID_STENCIL, (64, 64), k=4.0)
+    vg = kbl.make_vgrid(wl.grid.mode, wl.grid.n, wl.grid.lo, wl.grid.hi, wl.grid.k)
+    prm = kbl.make_params(wl.gamma, r_fac=wl.r_fac)
+    launch = lambda n_elem, per=5: kbl._lib.bounds_launch(prm, 2, n_elem, wl.n_s, per * n_elem, vg)
+    default = {n: launch(n) for n in (100, 2000, 14400, 20000, 100000)}
+    st, rp, cl = tensors(wl)
+    try:
+        idx = kbl.autotune_bounds(st, rp, cl, wl.n_s, vg, prm)
+        choice = (idx // 8, {5: -2, 6: -4, 0: 0}.get(idx % 8))
+        print(f"[tune] choice {choice}, defaults {default}", flush=True)
+        assert choice[0] == 14                      # 80 states on 64 x 64 nodes: culled
+        for n in (14400, 20000, 7300):
+            assert launch(n)[0] == choice[0]
+            if choice[1] is not None:
+                assert launch(n)[1] == choice[1]
+        for n in (100, 2000, 100000):
+            assert launch(n) == default[n]
+        assert launch(2000)[0] != 14
+        assert launch(14400, 9)[0] != 14            # 144 states: beyond the staged ones
+        # a choice on a small mesh does not take the place of the first
+        small = synth.make_quad_workload(N=12, seed=961, grid_nodes=64, name="tune_small")
+        s2, r2, c2 = tensors(small)
+        idx2 = kbl.autotune_bounds(s2, r2, c2, small.n_s, vg, prm)
+        assert launch(144)[0] == idx2 // 8 and launch(14400)[0] == choice[0]
+    finally:
+        kbl._lib.lib().kbl_autotune_clear()
+    assert launch(14400) == default[14400]
