@@ -187,8 +187,9 @@ kbl_status kbl_compute_bounds_nodes(const kbl_params* params, int32_t dim, int64
  * two or four elements per workgroup or as a persistent grid of 1, 2, 4 or 8
  * workgroups per compute unit (each workgroup then walks elements in a grid
  * stride).  Timing uses the first `sample_elems` elements (all when <= 0);
- * each candidate keeps the better of two trials, and the default launch is
- * kept unless another candidate is more than 3% faster.
+ * each candidate keeps the better of two trials, and the launch that a call
+ * takes without a choice (kbl_bounds_launch) is kept unless another candidate is
+ * more than 3% faster.
  * The choice is kept (per process) for later kbl_compute_bounds calls with
  * the same dimension, precision, grid size, nodes per element and grid mode, on
  * meshes within a factor of two of its elements and a quarter of its states per

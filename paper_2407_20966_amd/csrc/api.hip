@@ -212,26 +212,35 @@ int64_t default_blocks(const kbl::BoundsArgs& a, int dim, int prec, int tile) {
                                              : a.grid_blocks;
 }
 
-// The autotuned choice for this problem if there is one and it fits, else the
-// default (tile -1).  A choice made on a smaller mesh may not fit this one.
+// The default launch (tile -1 in 1D, where the grid decides).
+TuneVal default_launch(const kbl::BoundsArgs& a, int dim, int prec) {
+    TuneVal v{-1, default_blocks(a, dim, prec, -1)};
+    if (dim == 3) v.tile = kbl::bounds_default_tile_3d(a);
+    if (dim == 2 && prec == KBL_PREC_FP64) v.tile = kbl::bounds_default_tile_2d(a, &v.blocks);
+    if (dim == 2 && prec != KBL_PREC_FP64) v.tile = kbl::mixed_default_tile_2d(a.nx, a.ny, prec);
+    return v;
+}
+
+// The autotuned choice for this problem if there is one and it fits (one made on
+// another mesh may not), else the default.
 TuneVal tuned_or_default(const kbl::BoundsArgs& a, int dim, int prec) {
     TuneVal v;
-    if (tuned(tune_key(a, dim, prec), a.n_elem, a.nnz, &v) && (v.tile < 0 || tile_fits(a, dim, prec, v.tile)))
+    if (tuned(tune_key(a, dim, prec), a.n_elem, a.nnz, &v) &&
+        (v.tile < 0 || tile_fits(a, dim, prec, v.tile)))
         return v;
-    return TuneVal{-1, default_blocks(a, dim, prec, -1)};
+    return default_launch(a, dim, prec);
 }
 
 // The launch of a bounds call: a tuning-knob override, else an autotuned choice,
-// else the default (tile -1).
+// else the default.
 TuneVal choose_launch(const kbl::BoundsArgs& a, int dim, int prec) {
     TuneVal v{-1, a.grid_blocks};
     if (!a.energy_perstate) {
         v = tuned_or_default(a, dim, prec);
         if (const char* env = getenv(prec == KBL_PREC_FP64 ? "KBL_BOUNDS_TILE" : "KBL_MIXED_TILE")) {
-            if (v.tile < 0) v.blocks = default_blocks(a, dim, prec, atoi(env));
-            v.tile = atoi(env);
+            const int tile = atoi(env);
+            if (tile_fits(a, dim, prec, tile)) v = TuneVal{tile, default_blocks(a, dim, prec, tile)};
         }
-        if (!tile_fits(a, dim, prec, v.tile)) v.tile = -1;
     }
     if (const char* env = getenv("KBL_PERSISTENT_BLOCKS")) v.blocks = atoll(env);
     return v;
@@ -370,13 +379,7 @@ kbl_status kbl_bounds_launch(const kbl_params* params, int32_t dim, int64_t n_el
     const int prec = params->precision;
     rc = check_precision(a, dim, prec);
     if (rc != KBL_OK) return rc;
-    TuneVal v = choose_launch(a, dim, prec);
-    if (v.tile < 0 && !a.energy_perstate) {
-        a.grid_blocks = v.blocks;
-        if (dim == 3) v.tile = kbl::bounds_default_tile_3d(a);
-        if (dim == 2 && prec == KBL_PREC_FP64) v.tile = kbl::bounds_default_tile_2d(a, &v.blocks);
-        if (dim == 2 && prec != KBL_PREC_FP64) v.tile = kbl::mixed_default_tile_2d(a.nx, a.ny, prec);
-    }
+    const TuneVal v = choose_launch(a, dim, prec);
     *tile = v.tile < 0 ? 0 : v.tile;
     *blocks = v.blocks;
     return KBL_OK;
@@ -416,7 +419,9 @@ int32_t kbl_autotune_bounds(const kbl_params* params, int32_t dim, int64_t n_ele
     const int64_t shapes[] = {0, ncu, 2LL * ncu, 4LL * ncu, 8LL * ncu, -2, -4};
     constexpr int kShapes = sizeof(shapes) / sizeof(shapes[0]);
     static_assert(kShapes <= 8, "the result packs the shape in 3 bits");
-    const int def_shape = a.grid_blocks == -2 ? 5 : 0;
+    // what a call takes without a choice, left only for a measurable gain
+    const TuneVal def = default_launch(a, dim, prec);
+    const int def_tile = def.tile, def_shape = def.blocks == -2 ? 5 : 0;
     // time on a prefix of the elements (their rows are valid prefixes of the CSR)
     kbl::BoundsArgs s = a;
     s.n_elem = sample_elems > 0 && sample_elems < n_elem ? sample_elems : n_elem;
@@ -425,7 +430,7 @@ int32_t kbl_autotune_bounds(const kbl_params* params, int32_t dim, int64_t n_ele
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) return -1;
     // time each candidate twice (one warm-up, three launches per trial) and keep
-    // the better trial; leave the default launch only for a measurable gain
+    // the better trial
     auto time_candidate = [&](int t, int64_t b, float* ms_out) {
         s.grid_blocks = b;
         float best_trial = 1e30f;
@@ -441,10 +446,6 @@ int32_t kbl_autotune_bounds(const kbl_params* params, int32_t dim, int64_t n_ele
         *ms_out = best_trial;
         return true;
     };
-    const int def_tile = dim == 3   ? kbl::bounds_default_tile_3d(a.nx, a.ny, a.nz)
-                         : dim == 2 ? (prec == KBL_PREC_FP64 ? kbl::bounds_default_tile_2d(a.nx, a.ny)
-                                                             : kbl::mixed_default_tile_2d(a.nx, a.ny, prec))
-                                    : -1;
     // bring the clocks up first: the first launches after idle run slower, and
     // the default, timed first, would otherwise be measured at lower clocks
     s.grid_blocks = shapes[def_shape];

@@ -145,7 +145,6 @@ bool cull_pays(const BoundsArgs& a) {
 }  // namespace
 
 int bounds_tile_count_2d() { return kNumTiles2D; }
-int bounds_default_tile_2d(int nx, int ny) { return default_tile_2d(nx, ny); }
 
 int bounds_default_tile_2d(const BoundsArgs& a, int64_t* blocks) {
     *blocks = a.grid_blocks;
@@ -164,10 +163,8 @@ bool bounds_tile_fits_2d(int tile, const BoundsArgs& a) {
 hipError_t launch_bounds_fp64(const BoundsArgs& a, int dim, hipStream_t stream, int tile) {
     if (a.n_elem == 0) return hipSuccess;
     if (dim == 2) {
-        BoundsArgs b = a;
-        if (tile < 0) tile = bounds_default_tile_2d(a, &b.grid_blocks);
         if (!bounds_tile_fits_2d(tile, a)) return hipErrorInvalidValue;
-        return kTiles2D[tile].fn(b, stream);
+        return kTiles2D[tile].fn(a, stream);
     }
     return launch_bounds_fp64_1d(a, stream);
 }

@@ -398,9 +398,9 @@ bool bounds_tile_fits_3d(int tile, const BoundsArgs& a) {
 // Defaults: a thread tile that keeps two waves per SIMD (up to 18 nodes per
 // thread; at 24^3 the 3 x 3 x 2 tile measured fastest); kbl_autotune_bounds
 // may pick another.
-int bounds_default_tile_3d(int nx, int ny, int nz) {
-    (void)nz;
-    const int n = nx > ny ? nx : ny;
+int bounds_default_tile_3d(const BoundsArgs& a) {
+    if (cull_pays_3d(a)) return kCullTile3;
+    const int n = a.nx > a.ny ? a.nx : a.ny;
     if (n <= 16) return 0;
     if (n <= 24) return 6;
     if (n <= 32) return 2;
@@ -408,13 +408,8 @@ int bounds_default_tile_3d(int nx, int ny, int nz) {
     return 4;
 }
 
-int bounds_default_tile_3d(const BoundsArgs& a) {
-    return cull_pays_3d(a) ? kCullTile3 : bounds_default_tile_3d(a.nx, a.ny, a.nz);
-}
-
 hipError_t launch_bounds_fp64_3d(const BoundsArgs& a, hipStream_t stream, int tile) {
     if (a.n_elem == 0) return hipSuccess;
-    if (tile < 0) tile = bounds_default_tile_3d(a);
     if (!bounds_tile_fits_3d(tile, a)) return hipErrorInvalidValue;
     return kTiles3D[tile].fn(a, stream);
 }

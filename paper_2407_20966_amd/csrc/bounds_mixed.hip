@@ -630,7 +630,6 @@ int mixed_default_tile_2d(int nx, int ny, int precision) { return default_mixed_
 
 hipError_t launch_bounds_mixed(const BoundsArgs& a, int precision, hipStream_t stream, int tile) {
     if (a.n_elem == 0) return hipSuccess;
-    if (tile < 0 || !mixed_tile_fits(tile, a.nx, a.ny)) tile = default_mixed_tile(a.nx, a.ny, precision);
     if (!mixed_tile_fits(tile, a.nx, a.ny)) return hipErrorInvalidValue;
     const int slot = precision == KBL_PREC_MIXED_BF16 ? 0 : precision == KBL_PREC_MIXED_FP16 ? 1
                    : precision == KBL_PREC_MIXED_FP32 ? 2 : -1;

@@ -101,7 +101,7 @@ kbl_status make_limit_args_1d(const kbl_params* params, int32_t n_s, const doubl
 
 // Host-side launchers (one per translation unit).  They return hipSuccess or
 // the launch error; argument checking happened before.
-// tile < 0 selects the default 2D tile for the grid size.
+// tile: the 2D configuration (not used in 1D).
 hipError_t launch_bounds_fp64(const BoundsArgs& a, int dim, hipStream_t stream, int tile);
 hipError_t launch_bounds_fp64_1d(const BoundsArgs& a, hipStream_t stream);
 // The 16 x 16-thread tiles of one or 2 x 2 nodes per thread (nodes_per_thread 1, 2).
@@ -117,14 +117,12 @@ bool bounds_fp64_fit(const BoundsArgs& a);
 hipError_t launch_bounds_fp64_fit(const BoundsArgs& a, hipStream_t stream);
 // Energy bounds from the per-state integrand (KBL_FLAG_ENERGY_PERSTATE).
 hipError_t launch_bounds_fp64_energy(const BoundsArgs& a, int dim, hipStream_t stream);
-// d = 3: FP64 bounds over a 3D velocity grid (tile < 0: default for the grid).
+// d = 3: FP64 bounds over a 3D velocity grid.
 hipError_t launch_bounds_fp64_3d(const BoundsArgs& a, hipStream_t stream, int tile);
 int bounds_tile_count_3d();
 bool bounds_tile_fits_3d(int tile, const BoundsArgs& a);
-// The tile taken without a choice (for the grid alone: among those that evaluate
-// every pair).
+// The tile taken without a choice.
 int bounds_default_tile_3d(const BoundsArgs& a);
-int bounds_default_tile_3d(int nx, int ny, int nz);
 // The 2D kernel that culls states block by block (one wave per element).
 constexpr int kCullCap = 128;        // states of a stencil it can cull
 hipError_t launch_bounds_cull_2d(const BoundsArgs& a, hipStream_t stream);
@@ -135,15 +133,14 @@ hipError_t launch_bounds_cull_3d(const BoundsArgs& a, hipStream_t stream);
 bool bounds_cull_fits_3d(const BoundsArgs& a);
 int bounds_tile_count_2d();
 bool bounds_tile_fits_2d(int tile, const BoundsArgs& a);
-// The same in 2D; blocks: the launch shape it is taken with.
+// The tile taken without a choice in 2D; blocks: the launch shape it is taken with.
 int bounds_default_tile_2d(const BoundsArgs& a, int64_t* blocks);
 int mixed_tile_count();
-int bounds_default_tile_2d(int nx, int ny);
 int mixed_default_tile_2d(int nx, int ny, int precision);
 // The launch shape without a choice (tile < 0: of the default tile).
 int64_t mixed_default_blocks(const BoundsArgs& a, int precision, int tile);
 bool mixed_tile_fits_2d(int tile, int nx, int ny);
-// tile < 0 (or a tile that does not fit) selects the default for the grid size.
+// tile: a configuration that covers the grid.
 hipError_t launch_bounds_mixed(const BoundsArgs& a, int precision, hipStream_t stream, int tile);
 hipError_t launch_limit_fp64(const LimitArgs& a, int dim, hipStream_t stream);
 hipError_t launch_riemann_fp64(const RiemannArgs& a, int dim, hipStream_t stream);

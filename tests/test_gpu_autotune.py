@@ -48,3 +48,38 @@ def test_choice_holds_for_meshes_of_its_size(kbl, monkeypatch):  # noqa: F811
     finally:
         kbl._lib.lib().kbl_autotune_clear()
     assert launch(14400) == default[14400]
+
+
+@pytest.mark.parametrize("N,p,nodes", [(64, 1, 64), (60, 2, 40), (12, 3, 48), (140, 2, 64)])
+def test_tuned_is_not_slower_than_the_default(kbl, monkeypatch, N, p, nodes):  # noqa: F811
+    """The choice replaces the launch that a call takes without one only for a gain
+    of 3%; 1.06 leaves the timing's own spread."""
+    for k in ("KBL_BOUNDS_TILE", "KBL_MIXED_TILE", "KBL_PERSISTENT_BLOCKS"):
+        monkeypatch.delenv(k, raising=False)
+    wl = synth.make_quad_workload(N=N, p=p, seed=970, grid_nodes=nodes, name="tune_time")
+    vg = kbl.make_vgrid(wl.grid.mode, wl.grid.n, wl.grid.lo, wl.grid.hi, wl.grid.k)
+    prm = kbl.make_params(wl.gamma, r_fac=wl.r_fac)
+    st, rp, cl = tensors(wl)
+
+    def best_us():
+        times = []
+        for _ in range(12):
+            e0, e1 = torch.cuda.Event(True), torch.cuda.Event(True)
+            e0.record()
+            for _ in range(10):
+                kbl.compute_bounds(st, rp, cl, wl.n_s, vg, prm)
+            e1.record()
+            e1.synchronize()
+            times.append(e0.elapsed_time(e1) * 100.0)
+        return min(times)
+
+    try:
+        default = kbl._lib.bounds_launch(prm, 2, wl.n_elem, wl.n_s, wl.cols.size, vg)
+        before = best_us()
+        idx = kbl.autotune_bounds(st, rp, cl, wl.n_s, vg, prm)
+        after = best_us()
+        print(f"[tune] default {default} {before:.1f} us, choice {idx // 8}:{idx % 8} {after:.1f} us",
+              flush=True)
+        assert after <= 1.06 * before
+    finally:
+        kbl._lib.lib().kbl_autotune_clear()

@@ -120,3 +120,16 @@ def test_errors_are_those_of_the_call():
     with pytest.raises(L.KblError) as e:
         launch((24, 24, 24), 10, 1, 7, precision=L.PREC_MIXED_FP32)
     assert e.value.code == L.KBL_ERR_UNSUPPORTED
+
+
+def test_overrides_hold_over_the_default(monkeypatch):
+    assert launch((64, 64), 20000, 16, 80) == (14, 0)
+    monkeypatch.setenv("KBL_PERSISTENT_BLOCKS", "-2")
+    assert launch((64, 64), 20000, 16, 80) == (14, -2)
+    monkeypatch.setenv("KBL_BOUNDS_TILE", "12")
+    assert launch((64, 64), 20000, 16, 80) == (12, -2)
+    monkeypatch.setenv("KBL_BOUNDS_TILE", "1")      # does not cover the grid
+    assert launch((64, 64), 20000, 16, 80) == (14, -2)
+    monkeypatch.delenv("KBL_PERSISTENT_BLOCKS")
+    monkeypatch.setenv("KBL_BOUNDS_TILE", "12")
+    assert launch((64, 64), 2000, 16, 80) == (12, 0)
