@@ -247,14 +247,13 @@ def cull_ops(wl) -> float:
             + float(wl.n_elem) * wl.n_vel() * CULL_OPS_PER_NODE[wl.dim])
 
 
-def is_culled(wl, tuned) -> bool:
-    """Whether the FP64 bounds launch is the culling kernel (an autotuned
-    choice, or the default on large meshes and grids)."""
+def is_culled(kbl, wl, prm, vg) -> bool:
+    """Whether the FP64 bounds launch of a workload is the culling kernel, by the
+    library's own choice (autotuned or default)."""
     if wl.dim == 1:
         return False
-    if tuned:
-        return tuned["tile"] == CULL_TILE[wl.dim]
-    return max(wl.grid.n[:2]) > (24 if wl.dim == 2 else 16) and wl.n_elem >= 16384
+    tile, _ = kbl._lib.bounds_launch(prm, wl.dim, wl.n_elem, wl.n_s, wl.nnz, vg)
+    return tile == CULL_TILE[wl.dim]
 
 
 def cull_note(dim: int) -> str:
@@ -522,7 +521,7 @@ def time_3d(args, kbl, torch, synth, stream):
     l_ms = float(np.mean([e[1].elapsed_time(e[2]) for e in ev]))
     n_cu = torch.cuda.get_device_properties(dev).multi_processor_count
     kname, gthreads = kernel_shape(kbl, 3, tuned, wl.n_elem, n_cu)
-    culled = is_culled(wl, tuned)
+    culled = is_culled(kbl, wl, prm, vg)
     ops = cull_ops(wl) if culled else wl.pairs() * pair_ops(3)
     print(f"[bench] hex32: {ms:.3f} ms/step (bounds {b_ms:.3f} ms, limit {l_ms:.3f} ms)",
           file=sys.stderr, flush=True)
@@ -664,7 +663,7 @@ def fp64_leg(args, kbl, torch, d, stream, n_cu, label, steps):
     ms, b_ms, l_ms = time_step(kbl, torch, d, prm, prm, stream, steps, args.warmup)
     print(f"[bench] {label} fp64: {ms:.3f} ms/step (bounds {b_ms:.3f} ms, limit {l_ms:.3f} ms)",
           file=sys.stderr, flush=True)
-    culled = is_culled(wl, tuned)
+    culled = is_culled(kbl, wl, prm, d.vg)
     ops = cull_ops(wl) if culled else wl.pairs() * pair_ops(wl.dim)
     achieved = ops / (b_ms * 1e-3)
     kname, grid_threads = kernel_shape(kbl, wl.dim, tuned, wl.n_elem, n_cu)

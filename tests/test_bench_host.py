@@ -116,3 +116,27 @@ def test_write_traffic_from_counter_csvs(tmp_path, monkeypatch):
     text = tf.read_text()
     assert text.count("[entry]") == 2 and "workload = other" in text
     assert text.startswith("# header")
+
+
+@pytest.mark.parametrize("n,n_elem,n_s,states,culled", [
+    ((64, 64), 1048576, 16, 80, True), ((64, 64), 2000000, 6, 84, True),
+    ((64, 64), 20000, 36, 180, False),      # beyond the staged states
+    ((30, 16), 65536, 16, 80, False),       # split to fit the grid
+    ((28, 28), 20000, 16, 80, False), ((48, 48), 65536, 4, 20, False),
+    ((64, 64), 8000, 16, 80, True),         # fewer elements than it takes elsewhere
+    ((24, 24, 24), 32768, 27, 189, True), ((24, 24, 24), 32768, 1, 7, False),
+    ((24, 24, 24), 32768, 64, 448, False), ((40, 40, 40), 125, 8, 56, True),
+    ((64,), 100000, 4, 12, False)])
+def test_culled_launches_are_known_from_the_library(monkeypatch, n, n_elem, n_s, states, culled):
+    """Operations are counted by the kernel that the call takes: what the library
+    answers, not a rule of the benchmark's own."""
+    import types
+
+    import paper_2407_20966_amd as kbl
+    if not os.path.exists(kbl._lib.LIB_PATH):
+        pytest.skip("libkbl.so not built (run __graft_entry__.build())")
+    for k in ("KBL_BOUNDS_TILE", "KBL_PERSISTENT_BLOCKS"):
+        monkeypatch.delenv(k, raising=False)
+    wl = types.SimpleNamespace(dim=len(n), n_elem=n_elem, n_s=n_s, nnz=states // n_s * n_elem)
+    vg = kbl.make_vgrid(kbl.GRID_STENCIL, n, k=4.0)
+    assert bench.is_culled(kbl, wl, kbl.make_params(1.4), vg) == culled
