@@ -119,7 +119,7 @@ __attribute__((amdgpu_waves_per_eu(3))) void bounds_cull_3d(BoundsArgs p, CullGr
             if (tid == 0) store_nan<3>(p, e, KBL_ST_BAD_STENCIL);
             continue;
         }
-        int S = (int)(row1 - row0) * p.n_s;
+        const int S = (int)(row1 - row0) * p.n_s;
 
         // ---- prologue
         uint32_t bad = 0;
@@ -177,6 +177,7 @@ __attribute__((amdgpu_waves_per_eu(3))) void bounds_cull_3d(BoundsArgs p, CullGr
             continue;
         }
         const bool big = S > kCap;
+        int n_all = S;                   // states that an empty list stands for
         const bool all = big || any_cold;
 
         // relaxed sums of this thread: rho, E, momentum per direction; [0]
@@ -286,8 +287,7 @@ __attribute__((amdgpu_waves_per_eu(3))) void bounds_cull_3d(BoundsArgs p, CullGr
                 cn = finite ? cn : 0;
                 if (__ballot(cm + cn < 2 * S) == 0) {
                     // every block keeps every state: all may be the same (a constant
-                    // field), and the first then stands for all.  Every wave comes
-                    // here then and finds so.  (4096 hexahedra of 189 equal states on
+                    // field), and the first then stands for all.  (4096 hexahedra of 189 equal states on
                     // 24^3 nodes: 0.66 ms, 3.1 with all evaluated.)
                     const Rec3 f = L.rec[0];
                     bool differs = false;
@@ -297,7 +297,7 @@ __attribute__((amdgpu_waves_per_eu(3))) void bounds_cull_3d(BoundsArgs p, CullGr
                                    r.uz != f.uz || r.nk != f.nk;
                     }
                     if (__ballot(differs) == 0) {
-                        S = 1;
+                        n_all = 1;
                         cm = 0;
                         cn = 0;
                     }
@@ -408,8 +408,8 @@ __attribute__((amdgpu_waves_per_eu(3))) void bounds_cull_3d(BoundsArgs p, CullGr
                     // long lists: all states, both sides at once.  Stencils
                     // beyond the staged states go chunk by chunk, staged again
                     // for every pass (all waves make the same passes then).
-                    for (int c0 = 0; c0 < S; c0 += kCap) {
-                        const int cnt = S - c0 < kCap ? S - c0 : kCap;
+                    for (int c0 = 0; c0 < n_all; c0 += kCap) {
+                        const int cnt = n_all - c0 < kCap ? n_all - c0 : kCap;
                         if (big) {
                             __syncthreads();
                             if (tid < cnt) {
@@ -455,8 +455,8 @@ __attribute__((amdgpu_waves_per_eu(3))) void bounds_cull_3d(BoundsArgs p, CullGr
                         const double sg = side ? -1.0 : 1.0;
                         int n = (o >> (side ? 16 : 8)) & 255;
                         const uint8_t* lst = n ? L.list[side][blk] : L.all;
-                        const uint8_t* const end = lst + ((n ? n : S) - 1);
-                        n = !act ? 1 : n ? n : S;
+                        const uint8_t* const end = lst + ((n ? n : n_all) - 1);
+                        n = !act ? 1 : n ? n : n_all;
                         // the index of the next state is read one step ahead
                         int i = *lst;
                         auto next = [&]() {

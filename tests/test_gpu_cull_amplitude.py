@@ -7,7 +7,7 @@ import pytest
 
 import oracle
 import synth
-from synth.workloads import GRID_STENCIL, GridSpec
+from synth.workloads import GRID_GLOBAL, GRID_STENCIL, GridSpec
 from tests._parity import bounds_error, stencil_momentum_scale
 from tests.test_gpu_cull import TOL, kbl, run  # noqa: F401
 
@@ -96,3 +96,20 @@ def test_constant_stencils(kbl, monkeypatch):  # noqa: F811
 def test_constant_stencils_are_culled(kbl, monkeypatch, dim, n):  # noqa: F811
     us = timed(kbl, monkeypatch, dim, n, (1e-2, 0.0))
     assert us[0.0] <= us[1e-2]
+
+
+def test_constant_stencil_where_q_overflows(kbl, monkeypatch):  # noqa: F811
+    """A constant cold state at the corner of a box so long that q is finite in the
+    first of its four blocks only, the blocks of one wave in 3D: every wave deals the
+    passes alike all the same."""
+    for dim, plain in ((2, 1), (3, 6)):
+        wl = workload(dim, 3, 0.0)
+        wl.states = np.zeros_like(wl.states)
+        wl.states[0], wl.states[-1] = 1.0, 1e-150 / (wl.gamma - 1.0)
+        hi = (1e80,) + (1e-74,) * (dim - 1)
+        wl.grid = GridSpec(GRID_GLOBAL, (16,) + (18,) * (dim - 1), (0.0,) * dim, hi, 0.0)
+        print(f"[amplitude] {dim}D constant, q overflows", flush=True)
+        b, s = run(kbl, monkeypatch, wl, TILE[dim])
+        c, t = run(kbl, monkeypatch, wl, plain)
+        assert np.array_equal(s, t) and np.all(np.isfinite(c)) and np.all(c[0] > 1e50)
+        np.testing.assert_allclose(b, c, rtol=1e-12, atol=0.0)
