@@ -133,3 +133,30 @@ def test_overrides_hold_over_the_default(monkeypatch):
     monkeypatch.delenv("KBL_PERSISTENT_BLOCKS")
     monkeypatch.setenv("KBL_BOUNDS_TILE", "12")
     assert launch((64, 64), 2000, 16, 80) == (12, 0)
+
+
+# (grid, elements, nodes per element, states, tile): both sides of each threshold of
+# the 2D rule for quads of 80 states unless it is about the states or the nodes
+@pytest.mark.parametrize("n,n_elem,n_s,states,tile", [
+    ((64, 64), 2999, 16, 80, 12), ((64, 64), 3000, 16, 80, 14), ((49, 2), 3000, 16, 80, 14),
+    ((40, 40), 2999, 16, 80, 11), ((40, 40), 3000, 16, 80, 14),
+    ((48, 48), 8191, 16, 80, 11), ((48, 48), 8192, 16, 80, 14), ((48, 48), 10**6, 1, 48, 11),
+    ((48, 48), 10**6, 4, 36, 11), ((48, 48), 10**6, 4, 40, 14),
+    ((36, 41), 8191, 16, 80, 11), ((36, 41), 8192, 16, 80, 14),
+    ((32, 30), 8191, 16, 80, 1), ((32, 30), 8192, 16, 80, 14), ((32, 24), 10**6, 16, 80, 1),
+    ((28, 28), 32767, 16, 80, 1), ((28, 28), 32768, 16, 80, 14), ((28, 28), 10**6, 4, 60, 1),
+    ((24, 24), 10**6, 16, 80, 1), ((16, 16), 10**6, 16, 80, 0)])
+def test_2d_default_kernel(n, n_elem, n_s, states, tile):
+    assert launch(n, n_elem, n_s, states)[0] == tile
+
+
+def test_2d_default_elements_per_wave_or_workgroup():
+    assert [launch((64, 64), e, 16, 80)[1] for e in (2000, 65535, 65536)] == [0, 0, -2]
+    assert [launch((16, 16), e, 16, 80)[1] for e in (8191, 8192)] == [0, -2]
+
+
+@pytest.mark.parametrize("n,n_elem,tile", [
+    ((24, 24, 24), 511, 6), ((24, 24, 24), 512, 9), ((16, 16, 64), 10**5, 0), ((17, 2, 2), 512, 9),
+    ((30, 30, 30), 511, 2), ((33, 2, 2), 1, 9), ((2, 33, 2), 1, 9), ((40, 40, 40), 1, 9)])
+def test_3d_default_kernel(n, n_elem, tile):
+    assert launch(n, n_elem, 27, 189) == (tile, 0)
