@@ -19,10 +19,9 @@
 //       nk = -1 / (2 theta),  l = ln(theta delta / 2),
 //     staged in LDS, and the velocity box of eq. truncdomain.
 //  2. Cull, lane = block, two loops over the states.  The first finds the
-//     state r+ (r-) whose q is largest (smallest) at the block's centre, from the
-//     differences to the first state's q in FP32 (the values themselves, in
-//     FP32, tell states apart down to 2^-15 only; with references found so,
-//     flows that vary less within a stencil kept most states: 40000 quads of 80
+//     state r+ (r-) whose q is largest (smallest) at the block's centre, up to
+//     2^-44 of its value (in FP32, up to 2^-15, flows that vary less within a
+//     stencil had arbitrary references and kept most states: 40000 quads of 80
 //     states that differ by 1e-6 took 4.0 ms on 64 x 64 nodes, 1.9 now).  The
 //     second bounds q_i - q_r over the block: with the half widths wx, wy and
 //     the gradients 2 nk (c - U) at the centre c,
@@ -224,30 +223,22 @@ __attribute__((amdgpu_waves_per_eu(3))) void bounds_cull_2d(BoundsArgs p, CullGr
             const double wx = (xb - xa) * (1.0 + 1e-10) + 1e-14 * (fabs(xa) + fabs(xb));
             const double wy = (yb - ya) * (1.0 + 1e-10) + 1e-14 * (fabs(ya) + fabs(yb));
             const double Q = 0.25 * (wx * wx + wy * wy);
-            double v0;                   // q of the first state
-            {
-                const CullRec& r = L.rec[0];
-                const double dx = cx - r.ux, dy = cy - r.uy;
-                v0 = fma(r.nk, fma(dx, dx, dy * dy), r.a);
-            }
-            float kmax = 0.f, kmin = 0.f;
+            double kmax = -kInf, kmin = kInf;
 #pragma unroll 4
-            for (int s = 1; s < S; ++s) {
+            for (int s = 0; s < S; ++s) {
                 const CullRec& r = L.rec[s];
                 const double dx = cx - r.ux, dy = cy - r.uy;
-                const double v = fma(r.nk, fma(dx, dx, dy * dy), r.a - v0);
-                // the index in the low byte of the rounded difference: the state
-                // found is the extremum up to 2^-15 of the states' spread (any
-                // state is a valid reference)
-                const float key = __int_as_float((__float_as_int((float)v) & ~255) | s);
-                kmax = fmaxf(kmax, key);
-                kmin = fminf(kmin, key);
+                const double v = fma(r.nk, fma(dx, dx, dy * dy), r.a);
+                // the state's index in the low byte (any state is a valid reference)
+                const double key = __hiloint2double(__double2hiint(v), (__double2loint(v) & ~255) | s);
+                kmax = fmax(kmax, key);
+                kmin = fmin(kmin, key);
             }
             double vr[2], tr[2], sr[2], lr[2], qr[2];
             double slacks = 0.0;
 #pragma unroll
             for (int side = 0; side < 2; ++side) {
-                const int ref = __float_as_int(side ? kmin : kmax) & 127;
+                const int ref = __double2loint(side ? kmin : kmax) & 127;
                 const CullRec r = L.rec[ref];
                 const double dx = cx - r.ux, dy = cy - r.uy;
                 tr[side] = r.nk * dx;

@@ -5,9 +5,8 @@
 // block of velocity nodes few of the stencil's Maxwellians can be the largest
 // or the smallest, the others are excluded by bounding q_i - q_r over the block
 // against the state r that is extreme at its centre, and only the rest is
-// evaluated.  (r is found from differences of q here too: 4096 hexahedra of 189
-// states that differ by 1e-6 take 1.46 ms on 24^3 nodes, 3.26 with r found from
-// the values.)  Here q_i(u) = a_i + nk_i |u - U_i|^2 in three directions,
+// evaluated.  (4096 hexahedra of 189 states that differ by 1e-6 take 1.46 ms on
+// 24^3 nodes, 3.26 with r found in FP32.)  Here q_i(u) = a_i + nk_i |u - U_i|^2 in three directions,
 // a = ln rho - (3/2) ln(2 pi theta).
 //
 // One workgroup of four waves owns one element at a time.  The states' records
@@ -215,30 +214,23 @@ __attribute__((amdgpu_waves_per_eu(3))) void bounds_cull_3d(BoundsArgs p, CullGr
                     w[d] = (ub - ua) * (1.0 + 1e-10) + 1e-14 * (fabs(ua) + fabs(ub));
                     Q = fma(0.25 * w[d], w[d], Q);
                 }
-                float kmax = 0.f, kmin = 0.f;
-                double v0;               // q of the first state
-                {
-                    const Rec3& r = L.rec[0];
-                    const double dx = c[0] - r.ux, dy = c[1] - r.uy, dz = c[2] - r.uz;
-                    v0 = fma(r.nk, fma(dx, dx, fma(dy, dy, dz * dz)), r.a);
-                }
+                double kmax = -kInf, kmin = kInf;
 #pragma unroll 4
-                for (int s = 1; s < S; ++s) {
+                for (int s = 0; s < S; ++s) {
                     const Rec3& r = L.rec[s];
                     const double dx = c[0] - r.ux, dy = c[1] - r.uy, dz = c[2] - r.uz;
-                    const double v = fma(r.nk, fma(dx, dx, fma(dy, dy, dz * dz)), r.a - v0);
-                    // the index in the low byte of the rounded difference: the
-                    // state found is the extremum up to 2^-15 of the states'
-                    // spread (any state is a valid reference)
-                    const float key = __int_as_float((__float_as_int((float)v) & ~255) | s);
-                    kmax = fmaxf(kmax, key);
-                    kmin = fminf(kmin, key);
+                    const double v = fma(r.nk, fma(dx, dx, fma(dy, dy, dz * dz)), r.a);
+                    // the state's index in the low byte (any state is a valid
+                    // reference)
+                    const double key = __hiloint2double(__double2hiint(v), (__double2loint(v) & ~255) | s);
+                    kmax = fmax(kmax, key);
+                    kmin = fmin(kmin, key);
                 }
                 double vr[2], tr[2][3], lr[2], qr[2];
                 double slacks = 0.0;
 #pragma unroll
                 for (int sd = 0; sd < 2; ++sd) {
-                    const Rec3 r = L.rec[__float_as_int(sd ? kmin : kmax) & 255];
+                    const Rec3 r = L.rec[__double2loint(sd ? kmin : kmax) & 255];
                     const double dx = c[0] - r.ux, dy = c[1] - r.uy, dz = c[2] - r.uz;
                     tr[sd][0] = r.nk * dx;
                     tr[sd][1] = r.nk * dy;
@@ -261,7 +253,7 @@ __attribute__((amdgpu_waves_per_eu(3))) void bounds_cull_3d(BoundsArgs p, CullGr
                 uint8_t* const row_l = L.list[1][ot];
                 cm = 0;
                 cn = 0;
-#pragma unroll 2
+#pragma unroll 4
                 for (int s = 0; s < S; ++s) {
                     const Rec3& r = L.rec[s];
                     const double dx = c[0] - r.ux, dy = c[1] - r.uy, dz = c[2] - r.uz;
