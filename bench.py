@@ -67,6 +67,7 @@ WORKLOAD_TEXT = {
 # sources of the FP64 bounds kernels, per velocity dimension
 KERNEL_SOURCES = {
     2: ("paper_2407_20966_amd/csrc/bounds_fp64.hip", "paper_2407_20966_amd/csrc/bounds_2d.h",
+        "paper_2407_20966_amd/csrc/thread_split.h",
         "paper_2407_20966_amd/csrc/bounds_fp64_small.hip",
         "paper_2407_20966_amd/csrc/bounds_cull_2d.hip",
         "paper_2407_20966_amd/csrc/bounds_common.h",
@@ -77,6 +78,12 @@ KERNEL_SOURCES = {
         "paper_2407_20966_amd/csrc/exp2_table.h"),
 }
 TRAFFIC_FILE = "profiles/bounds_fp64_traffic.txt"
+CULL_TRAFFIC_FILE = "profiles/bounds_cull_traffic.txt"
+
+
+def traffic_file(kernel: str) -> str:
+    """The committed counter summary that holds a kernel's entries."""
+    return CULL_TRAFFIC_FILE if kernel.startswith("bounds_cull_") else TRAFFIC_FILE
 
 
 def kernel_sources_sha(dim: int) -> str:
@@ -98,7 +105,7 @@ def profiled_traffic(kernel: str, grid_threads: int, workload: str, dim: int):
     preferred; else one of the same kernel at another grid size (the autotuner
     may pick a persistent grid: the same element work, so the same bytes up to
     L2 reuse)."""
-    path = os.path.join(ROOT, TRAFFIC_FILE)
+    path = os.path.join(ROOT, traffic_file(kernel))
     if not os.path.exists(path) or dim not in KERNEL_SOURCES:
         return None, None
     entries, cur = [], None
@@ -145,7 +152,7 @@ def _counter_per_dispatch(csv_path: str, counter: str):
 
 def write_traffic(workload: str, fetch_csv: str, write_csv: str) -> dict:
     """Turns a FETCH_SIZE run and a WRITE_SIZE run of bench.py (each with
-    --copy-calibration) into an entry of the traffic file, replacing an entry
+    --copy-calibration) into an entry of the kernel's traffic file, replacing an entry
     of the same workload, kernel and grid and the workload's entries of older
     sources.  Calibration: the device copy reads
     as many bytes as it writes, and WRITE_SIZE counts the bytes written, so
@@ -167,8 +174,9 @@ def write_traffic(workload: str, fetch_csv: str, write_csv: str) -> dict:
     def bounds_launches(d):
         runs, last = {}, None
         for name, grid, v in d.values():               # in dispatch order
-            if "bounds_fp64_" in name and "bwd" not in name:
+            if ("bounds_fp64_" in name or "bounds_cull_" in name) and "bwd" not in name:
                 kname = name.replace("void kbl::(anonymous namespace)::", "").split("(kbl")[0]
+                kname = kname.replace("kbl::(anonymous namespace)::", "")
                 runs.setdefault((kname, grid), []).append(v)
                 last = (kname, grid)
         # the timed launches come last (after the autotuner's candidates)
@@ -190,9 +198,9 @@ def write_traffic(workload: str, fetch_csv: str, write_csv: str) -> dict:
              "fetch_kib_per_dispatch": f"{f_kib:.1f}", "write_kib_per_dispatch": f"{w_kib:.1f}",
              "fetch_scale": f"{scale:.4f}", "bytes_per_launch": f"{nbytes:.0f}",
              "algorithmic_bytes_per_launch": str(alg)}
-    path = os.path.join(ROOT, TRAFFIC_FILE)
+    path = os.path.join(ROOT, traffic_file(kname))
     head, blocks = [], []
-    for line in open(path):
+    for line in (open(path) if os.path.exists(path) else ()):
         if line.strip() == "[entry]":
             blocks.append([])
         (blocks[-1] if blocks else head).append(line)
@@ -671,7 +679,7 @@ def fp64_leg(args, kbl, torch, d, stream, n_cu, label, steps):
                              if grid_threads else (None, None))
     roof = {"bound": "alu", "achieved": achieved / 1e12, "peak": VALU_PEAK_OPS / 1e12,
             "unit": "TOP/s", "frac": achieved / VALU_PEAK_OPS, "traffic": traffic,
-            "traffic_unit": "bytes per launch", "traffic_source": TRAFFIC_FILE,
+            "traffic_unit": "bytes per launch", "traffic_source": traffic_file(kname),
             "traffic_grid_threads": traffic_grid, "kernel": kname, "grid_threads": grid_threads,
             "ops_per_launch": ops, "pairs_per_launch": wl.pairs(),
             "ops_per_pair": pair_ops(wl.dim), "kernel_ms": b_ms, "limit_ms": l_ms,
@@ -867,7 +875,8 @@ def main(argv=None):
                     help="also run one plain device copy of MIB MiB (counter calibration)")
     ap.add_argument("--write-traffic", nargs=2, metavar=("FETCH_CSV", "WRITE_CSV"),
                     help="no timing: turn the counter CSVs of a FETCH_SIZE and a WRITE_SIZE "
-                         "run on --workload into its entry of " + TRAFFIC_FILE)
+                         "run on --workload into its entry of " + TRAFFIC_FILE +
+                         " (the culling kernels': " + CULL_TRAFFIC_FILE + ")")
     args = ap.parse_args(argv)
     if args.write_traffic:
         e = write_traffic(args.workload, *args.write_traffic)

@@ -118,6 +118,27 @@ def test_write_traffic_from_counter_csvs(tmp_path, monkeypatch):
     assert text.startswith("# header")
 
 
+def test_write_traffic_of_a_culling_launch(tmp_path, monkeypatch):
+    """The culling kernel is a FP64 bounds launch like the others (the autotuner's
+    candidates of the other kernels come before it); its entries stand in their own
+    file, from which they are read back."""
+    (tmp_path / "profiles").mkdir()
+    (tmp_path / bench.TRAFFIC_FILE).write_text("# header\n")
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    monkeypatch.setattr(bench, "kernel_sources_sha", lambda dim: "ab" * 32)
+    table = "void kbl::(anonymous namespace)::bounds_fp64_2d<16, 16, 3, 3, 2, 0>(kbl::BoundsArgs)"
+    cull = ("kbl::(anonymous namespace)::bounds_cull_2d(kbl::BoundsArgs, "
+            "kbl::(anonymous namespace)::CullGrid)")
+    for f, n, v in (("f.csv", "FETCH_SIZE", 500.0), ("w.csv", "WRITE_SIZE", 1000.0)):
+        _counter_csv(tmp_path / f, n, [("__amd_rocclr_copyBuffer", 1024, v),
+                                       (table, 4096, 9.0), (cull, 8192, 1e5)])
+    e = bench.write_traffic("quad256", str(tmp_path / "f.csv"), str(tmp_path / "w.csv"))
+    assert (e["kernel"], e["grid_threads"]) == ("bounds_cull_2d", "8192")
+    assert (tmp_path / bench.TRAFFIC_FILE).read_text() == "# header\n"
+    got = bench.profiled_traffic("bounds_cull_2d", 8192, "quad256", 2)
+    assert got == (pytest.approx(3e5 * 1024.0), 8192)
+
+
 @pytest.mark.parametrize("n,n_elem,n_s,states,culled", [
     ((64, 64), 1048576, 16, 80, True), ((64, 64), 2000000, 6, 84, True),
     ((64, 64), 20000, 36, 180, False),      # beyond the staged states
