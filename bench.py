@@ -23,6 +23,7 @@ from __future__ import annotations
 import argparse
 import json
 import os
+import re
 import sys
 import time
 
@@ -177,6 +178,9 @@ def write_traffic(workload: str, fetch_csv: str, write_csv: str) -> dict:
             if ("bounds_fp64_" in name or "bounds_cull_" in name) and "bwd" not in name:
                 kname = name.replace("void kbl::(anonymous namespace)::", "").split("(kbl")[0]
                 kname = kname.replace("kbl::(anonymous namespace)::", "")
+                # without the 2D tiles' last parameter, their threads' split to the
+                # grid: it goes with the workload, and kernel_shape does not name it
+                kname = re.sub(r"(bounds_fp64_2d<(?:\d+, ){4}\d+), \d+>", r"\1>", kname)
                 runs.setdefault((kname, grid), []).append(v)
                 last = (kname, grid)
         # the timed launches come last (after the autotuner's candidates)

@@ -139,6 +139,23 @@ def test_write_traffic_of_a_culling_launch(tmp_path, monkeypatch):
     assert got == (pytest.approx(3e5 * 1024.0), 8192)
 
 
+def test_write_traffic_names_the_tile_as_the_lookup_does(tmp_path, monkeypatch):
+    """A 2D tile's entry carries the name that kernel_shape gives its launch."""
+    import paper_2407_20966_amd as kbl
+    (tmp_path / "profiles").mkdir()
+    (tmp_path / bench.TRAFFIC_FILE).write_text("# header\n")
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    monkeypatch.setattr(bench, "kernel_sources_sha", lambda dim: "ab" * 32)
+    name, grid = bench.kernel_shape(kbl, 2, {"tile": 11, "elements_per_workgroup": 2}, 65536, 256)
+    for f, n, v in (("f.csv", "FETCH_SIZE", 500.0), ("w.csv", "WRITE_SIZE", 1000.0)):
+        _counter_csv(tmp_path / f, n, [
+            ("__amd_rocclr_copyBuffer", 1024, v),
+            (f"void kbl::(anonymous namespace)::{name[:-1]}, 48>(kbl::BoundsArgs)", grid, 1e5)])
+    e = bench.write_traffic("quad256", str(tmp_path / "f.csv"), str(tmp_path / "w.csv"))
+    assert (e["kernel"], e["grid_threads"]) == (name, str(grid))
+    assert bench.profiled_traffic(name, grid, "quad256", 2)[1] == grid
+
+
 @pytest.mark.parametrize("n,n_elem,n_s,states,culled", [
     ((64, 64), 1048576, 16, 80, True), ((64, 64), 2000000, 6, 84, True),
     ((64, 64), 20000, 36, 180, False),      # beyond the staged states
