@@ -588,13 +588,13 @@ def time_fr1d(args, kbl, torch, stream):
           f"{ms_graph:.3f} with the device CFL step in HIP graphs over {n_graph} steps)",
           file=sys.stderr, flush=True)
     return {"workload": "Sod shock tube, FR p=3, 3200 elements, HLLC, SSP-RK3 with the kinetic "
-                        "bounds (k=8, 2048 velocity nodes, node stencils of 10 states) and the "
+                        "bounds (k=8, 2048 velocity nodes, stencils of 8 states) and the "
                         "squeeze limiter after every stage",
             "ms_per_step": ms, "steps_per_s": 1e3 / ms, "ms_per_step_with_cfl_sync": ms_cfl,
             "ms_per_step_device_cfl_graph": ms_graph, "graph_steps": n_graph,
             "element_stages_per_s": 3 * pr.n_elem / (ms * 1e-3),
             "bounds_pairs_per_step": pairs,
-            "launches_per_step": 14}
+            "launches_per_step": 3}
 
 
 class Dev:
