@@ -173,12 +173,21 @@ kbl_status kbl_compute_bounds_nodes(const kbl_params* params, int32_t dim, int64
  *   KBL_PERSISTENT_BLOCKS=<g>  grid of g workgroups walking the elements
  *                              (0 = one workgroup per element, -k = k
  *                              elements per workgroup)
- * Without either, a 2D launch from 8192 elements on has each workgroup compute
- * two elements (half as many workgroups as elements), a smaller one and a 1D
- * or 3D launch one workgroup per element.  The 2D FP64 tile 14 has one element
- * per wave, four waves per workgroup: there a choice of k elements per
- * workgroup means k per wave, and large 2D launches use it with two elements
- * per wave (one below 65536 elements).
+ * Without either, a 2D FP64 launch from 8192 elements on has each workgroup
+ * compute two elements (half as many workgroups as elements), a smaller one and
+ * a 1D or 3D launch one workgroup per element; a mixed launch does so by its tile,
+ * elements and states.  The 2D FP64 tile 14 has one element per wave, four waves
+ * per workgroup: there a choice of k elements per workgroup means k per wave.
+ *
+ * Which kernel is the default depends on the velocity grid, the number of
+ * elements and the mean number of states per element (tile 14 in 2D and tile 9 in
+ * 3D leave out states that cannot win, on meshes large enough for it); the
+ * autotuner's choice depends on what it timed.  The kernels add up in different
+ * orders, so an element's bounds can differ in the last bits between a call on
+ * part of a mesh and one on all of it, or from run to run of the autotuner.
+ * With one kernel (KBL_BOUNDS_TILE, or the same sizes and no autotuning) the
+ * results are bitwise the same for every launch shape.  kbl_bounds_launch says
+ * which kernel a call would take.
  */
 /*
  * kbl_autotune_bounds - picks the launch configuration of kbl_compute_bounds

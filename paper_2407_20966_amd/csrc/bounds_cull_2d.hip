@@ -43,14 +43,20 @@
 //  5. One reduction over the wave, relaxation (eq. relaxed), floor, store.
 // The order of all sums is fixed: results are bitwise deterministic.
 //
-// What bounds it: VALU issue (83% busy at three waves per SIMD).  Two million
-// triangles on a 64 x 64 grid take 69 ms against 148 ms for evaluating every
-// pair (bounds_fp64_2d), 18.0k VALU instructions per element against 40k: the
-// cull 3.7k, 16 passes of about 430 besides the list states, 30 per list step.
-// 512^2 quads on a global 64 x 64 grid: 8.7 against 19.0 ms; 256^2 quads on a
-// 48 x 48 per-stencil grid, whose blocks near ties keep long lists: 2.4
-// against 2.9 ms.  Four waves per SIMD (128 VGPRs) spilled in the loops and
-// ran 25% slower.
+// What bounds it: VALU issue (88% busy at three waves per SIMD; these are the
+// counters of the case tri_1000, kept under profiles/).  Two million triangles on
+// a 64 x 64 grid take 67.4 ms against 147.4 ms for evaluating every pair
+// (bounds_fp64_2d), 16.8k VALU instructions per element against 39.7k: the cull
+// 3.8k, 16 passes of about 430 besides the list states, 35 per list step.  With
+// the limiter, 512^2 quads on a global 64 x 64 grid take 8.6 against 19.0 ms;
+// 256^2 quads on a 48 x 48 per-stencil grid, whose blocks near ties keep long
+// lists, 2.80 against 3.20 ms with the limiter and the backward (85% busy).  At
+// three waves 110 values wait in scratch outside the inner loops: 88 GB per launch
+// on the triangles, 1.3 TB/s, a third of a copy's rate.  Four waves per SIMD (128
+// VGPRs) spilled in the loops and ran 25% slower.
+// Where it loses: states that tie up to rounding but are not equal (a uniform
+// flow after a few steps).  No block can leave out any, and q is formed for 2 x 2
+// nodes at a time: 40000 quads of 80 such states take 4.2 ms against 2.95.
 //
 // Rounding: the bounds of step 2 are computed in FP64, half widths widened by 1e-10
 // and thresholds by 1e-12 relative, far above their rounding error.

@@ -20,9 +20,12 @@
 // 15-20 states per side on average (3-4 in the median block) against 43-52
 // for blocks of 6 nodes, whose cull costs a quarter.
 //
-// What bounds it: VALU issue and latency (57-65% busy at three waves per SIMD;
-// 154k VALU instructions per element on 24^3 nodes and 189 states, against
-// 294k for every pair).  32^3 hexahedra: 10.5 against 17.7 ms (bounds_fp64_3d).
+// What bounds it: VALU issue and latency (80% busy at three waves per SIMD, by the
+// counters of the case hex_32 kept under profiles/; 154k VALU instructions per element on 24^3 nodes
+// and 189 states, against 294k for every pair).  32^3 hexahedra with the limiter:
+// 10.5 against 17.7 ms (bounds_fp64_3d).  States that tie up to rounding but are
+// not equal are all evaluated: 4096 hexahedra 3.1 against 2.25 ms.  Values kept in
+// scratch outside the list loops move 9.8 GB per launch of 32^3 (0.9 TB/s).
 // Sorting all blocks of an element instead of each wave's own, and dealing
 // the passes by their work, took it from 12.3 to 11.7 ms; list addresses kept
 // out of scratch from 11.7 to 11.0 ms.

@@ -12,14 +12,15 @@ namespace {
 // four exps and the moments.  Two nodes per thread and round and at most 96
 // VGPRs keep five waves on a SIMD to cover the prologue, the exp table reads
 // and the barriers: 20000 stencils of 12 states take 253 us with 2048 nodes,
-// 9 states 140 with 1000, 12 states 108 with 500 (290, 171 and 118 with all of
-// a thread's nodes at once, in up to 168 VGPRs; four nodes per round, four
-// waves: 254, 145, 159); 30000 with 200 nodes take 124 us against 144.
+// 9 states 142 with 1000 (290 and 171 with all of a thread's nodes at once, in up
+// to 168 VGPRs; four nodes per round, four waves: 254, 145); 30000 with 200 nodes
+// take 125 us against 144.  Up to 512 nodes there is one round in any case (the
+// rule below).
 // CULL (grids beyond 512 nodes, ten states and more): a wave's 128 nodes of a
 // round are a block over which five of 12 or seven of 18 states can be an
 // extremum.  Lane = (round, state) bounds up to four rounds at once, the ballot is
-// the mask of states to visit.  2048 nodes: 12 states 203 us against 253, 18
-// states 231 against 315; 700 nodes, 12 states 132 against 153; where states
+// the mask of states to visit.  2048 nodes: 12 states 205 us against 253, 18
+// states 234 against 315; 700 nodes, 12 states 137 against 153; where states
 // tie up to rounding all are visited in the plain loop, of equal states one is
 // (20000 stencils of 12 on 1100 nodes: 133 us, 195 with all, 254 before the cull).
 // The 1D solver's stencils of 6 to 12 states gain nothing by it.
